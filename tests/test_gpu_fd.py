@@ -61,3 +61,40 @@ def test_fd2d_256_grid_mode_decay(cuda):
     r = mu * dt / dx ** 2
     lam = 1 - 4 * r * (np.sin(2 * np.pi * dx / 2) ** 2 + np.sin(3 * np.pi * dx / 2) ** 2)
     np.testing.assert_allclose(u[0].cpu().numpy(), lam ** 100 * u0, rtol=0, atol=1e-12)
+
+
+# tiles of 64 x 128 nodes: one tile (all substeps in one launch), its edges,
+# two tiles in either direction, odd and even launch counts
+@pytest.mark.parametrize("per_node", [False, True])
+@pytest.mark.parametrize("nx,ny,n_grid,steps", [(1, 7, 2, 3), (3, 3, 1, 5), (17, 19, 3, 40), (64, 128, 2, 33),
+                                                (65, 128, 1, 1), (64, 129, 2, 29), (130, 257, 2, 50),
+                                                (200, 64, 5, 26)])
+def test_fd2d_tiles_bit_exact(cuda, nx, ny, n_grid, steps, per_node):
+    import torch
+    from paper_2206_02607_amd import crom
+    g = rng(nx * 1000 + ny)
+    u0 = g.uniform(-1, 1, size=(n_grid, nx, ny)) * 10.0 ** g.integers(-250, 3, size=(n_grid, nx, ny))
+    nu = g.uniform(0.1, 1.0, size=(n_grid, nx, ny) if per_node else n_grid)
+    dx = 1.0 / 126.7
+    dt = 0.2 * dx * dx
+    u = torch.from_numpy(u0.copy()).to(cuda)
+    crom.fd_heat(u, torch.from_numpy(np.ascontiguousarray(nu)).to(cuda), dx, dt, steps)
+    for k in range(n_grid):
+        np.testing.assert_array_equal(u[k].cpu().numpy(), heat.fd_heat2d(u0[k], nu[k], dx, dt, steps))
+
+
+@pytest.mark.parametrize("dx,amp", [(1e-3, 1e150), (0.1, 1e302), (1e-40, 1.0)])
+def test_fd2d_overflow(cuda, dx, amp):
+    """Unstable and huge fields: infinities and NaN where the plain
+    evaluation has them, one tile (in place) and several."""
+    import torch
+    from paper_2206_02607_amd import crom
+    for nx, ny in ((40, 50), (150, 90)):
+        u0 = rng(5).uniform(-1, 1, size=(1, nx, ny)) * amp
+        u0[0, :, ny // 2:] = 0.0
+        dt = 40.0 * dx * dx
+        u = torch.from_numpy(u0.copy()).to(cuda)
+        crom.fd_heat(u, torch.ones(1, dtype=torch.float64, device=cuda), dx, dt, 90)
+        with np.errstate(all="ignore"):
+            ref = heat.fd_heat2d(u0[0], 1.0, dx, dt, 90)
+        np.testing.assert_array_equal(u[0].cpu().numpy(), ref)
