@@ -13,6 +13,7 @@
 // FP32 kernels with a fixed summation order.
 #include "common.hpp"
 #include "gemm.hpp"
+#include "train_fused.hpp"
 
 namespace crom {
 
@@ -261,15 +262,20 @@ __global__ __launch_bounds__(256) void colsum_final_kernel(const double* __restr
     out[(int64_t)seg * n_out + o] = ((sh[0][threadIdx.x] + sh[1][threadIdx.x]) + sh[2][threadIdx.x]) + sh[3][threadIdx.x];
 }
 
+constexpr int COLSUM_CHUNKS = 2048;  // partial sums per column sum at most
+// Chunks of a snapshot's rows in the column sums (at most COLSUM_CHUNKS, or
+// one per segment, in all).
+static int row_chunks(int64_t rows, int segs) {
+  const int64_t chunks = (rows + 255) / 256, cap = max(1, COLSUM_CHUNKS / segs);
+  return (int)(chunks > cap ? cap : chunks < 1 ? 1 : chunks);
+}
+
 // Column sums of X [segs * seg_rows][cols] (leading dimension ldx) per
 // segment, weighted as in colsum_kernel, into out [segs][nw][cols] (FP64).
 template <class T>
 static void colsum(const T* X, int64_t ldx, int cols, int segs, int64_t seg_rows, const float* wt, int64_t wmod,
-                   int wstride, int nw, double* part, int max_chunks, double* out, hipStream_t st) {
-  int chunks = (int)((seg_rows + 255) / 256);
-  const int cap = max(1, max_chunks / segs);
-  if (chunks > cap) chunks = cap;
-  if (chunks < 1) chunks = 1;
+                   int wstride, int nw, double* part, double* out, hipStream_t st) {
+  const int chunks = row_chunks(seg_rows, segs);
   const int chunk_rows = (int)((seg_rows + chunks - 1) / chunks);
   constexpr int VEC = 16 / (int)sizeof(T);
   if (cols % VEC == 0 && ldx % VEC == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0)
@@ -286,29 +292,34 @@ static void colsum(const T* X, int64_t ldx, int cols, int segs, int64_t seg_rows
 // S[b][1 + i][u] = sum_p dz1 x_p[i] (i < m):
 //   dW1[u][i] = sum_b S[b][1+i][u]; dW1[u][m+k] = sum_b S[b][0][u] q[b][k];
 //   db1[u] = sum_b S[b][0][u];  dq[b][k] = sum_u S[b][0][u] W1[u][m+k]
-__global__ void layer1_grad_kernel(const double* __restrict__ S, const float* __restrict__ q, const float* __restrict__ W1,
-                                   int B, int W, int m, int r, float* __restrict__ dW1, float* __restrict__ db1,
-                                   float* __restrict__ dq) {
-  const int nw = 1 + m;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < W * (m + r) + W + B * r; i += gridDim.x * blockDim.x) {
-    if (i < W * (m + r)) {
-      const int u = i / (m + r), k = i % (m + r);
-      double s = 0.0;
-      for (int b = 0; b < B; ++b)
-        s += k < m ? S[((int64_t)b * nw + 1 + k) * W + u] : S[((int64_t)b * nw) * W + u] * (double)q[b * r + (k - m)];
-      dW1[i] = (float)s;
-    } else if (i < W * (m + r) + W) {
-      const int u = i - W * (m + r);
-      double s = 0.0;
-      for (int b = 0; b < B; ++b) s += S[((int64_t)b * nw) * W + u];
-      db1[u] = (float)s;
-    } else {
-      const int j = i - W * (m + r) - W, b = j / r, k = j % r;
-      double s = 0.0;
-      for (int u = 0; u < W; ++u) s += S[((int64_t)b * nw) * W + u] * (double)W1[u * (m + r) + m + k];
-      dq[j] = (float)s;
-    }
+// One wave per output, its lanes over the sum (a thread per output, with
+// the sum as a chain of dependent loads, took 22 us for 16 snapshots).
+__global__ __launch_bounds__(256) void layer1_grad_kernel(const double* __restrict__ S, const float* __restrict__ q,
+                                                          const float* __restrict__ W1, int B, int W, int m, int r,
+                                                          float* __restrict__ dW1, float* __restrict__ db1,
+                                                          float* __restrict__ dq) {
+  const int nw = 1 + m, lane = threadIdx.x & 63;
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (i >= W * (m + r) + W + B * r) return;
+  double s = 0.0;
+  float* out;
+  if (i < W * (m + r)) {
+    const int u = i / (m + r), k = i % (m + r);
+    for (int b = lane; b < B; b += 64)
+      s += k < m ? S[((int64_t)b * nw + 1 + k) * W + u] : S[((int64_t)b * nw) * W + u] * (double)q[b * r + (k - m)];
+    out = dW1 + i;
+  } else if (i < W * (m + r) + W) {
+    const int u = i - W * (m + r);
+    for (int b = lane; b < B; b += 64) s += S[((int64_t)b * nw) * W + u];
+    out = db1 + u;
+  } else {
+    const int j = i - W * (m + r) - W, b = j / r, k = j % r;
+    for (int u = lane; u < W; u += 64) s += S[((int64_t)b * nw) * W + u] * (double)W1[u * (m + r) + m + k];
+    out = dq + j;
   }
+#pragma unroll
+  for (int w = 1; w < 64; w <<= 1) s += __shfl_xor(s, w);
+  if (lane == 0) *out = (float)s;
 }
 
 __global__ void d2f_kernel(const double* __restrict__ a, float* __restrict__ b, int64_t n) {
@@ -434,8 +445,15 @@ struct Carve {
   }
 };
 
-constexpr int COLSUM_CHUNKS = 2048;  // partial sums per column sum at most
 constexpr int MSE_BLOCKS = 1024;
+
+// The shapes the fused pass is compiled for: its LDS holds one activation
+// tile per product and the registers its weight gradients, four at most.
+// It is the faster path at every size (one snapshot of 64 points: MEASURED).
+static bool fused_shape(const crom_net* n) {
+  return n->width == TF_W && n->m == 2 && n->d == 1 && n->act == CROM_ACT_ELU && n->depth >= 3 && n->depth <= 5 &&
+         n->precision != CROM_PREC_FP32;
+}
 
 // The decoder's forward and backward over B snapshots x P points.  q: [B][r]
 // FP32 latents.  dg_in: when not NULL the caller's dL/dg [B*P][D] (no loss);
@@ -447,6 +465,7 @@ struct DecoderPass {
   T* gt[16];  // sine networks: cos(z_l) of each hidden layer
   float *c, *g, *dg, *part;
   double *cpart, *csum, *mpart;
+  bf16x8* frags;  // the fused pass: packed weights
   static size_t bytes(const crom_net* n, int B, int64_t P) {
     Carve cv{nullptr, 0};
     DecoderPass d;
@@ -456,6 +475,16 @@ struct DecoderPass {
   void carve(Carve& cv, const crom_net* n, int B, int64_t P) {
     const int64_t rows = (int64_t)B * P;
     const int W = n->width, depth = n->depth, D = n->d;
+    if (fused_shape(n)) {
+      const int64_t items = (int64_t)B * row_chunks(P, B), wgs = items < TF_MAX_WG ? items : TF_MAX_WG;
+      frags = cv.take<bf16x8>((size_t)(depth - 1) * 2 * TF_FRAGS);
+      c = cv.take<float>((size_t)B * W);
+      part = cv.take<float>((size_t)wgs * (depth - 1) * TF_MAT);
+      cpart = cv.take<double>((size_t)items * 3 * W);
+      mpart = cv.take<double>((size_t)wgs * (2 * W + 2));
+      csum = cv.take<double>((size_t)B * 3 * W);
+      return;
+    }
     for (int l = 0; l < depth; ++l) a[l] = cv.take<T>((size_t)rows * W);
     for (int l = 0; l < depth; ++l) gt[l] = n->act == CROM_ACT_SINE ? cv.take<T>((size_t)rows * W) : nullptr;
     dz0 = cv.take<T>((size_t)rows * W);
@@ -473,6 +502,45 @@ struct DecoderPass {
   }
 };
 
+template <int L>
+static crom_status fused_fwd_bwd(const crom_net* n, const float* x, int B, int64_t P, const float* q, const float* u,
+                                 const float* dg_in, float* grad, float* dq, float* loss, DecoderPass<__bf16>& ws,
+                                 hipStream_t st) {
+  const int r = n->r;
+  const ParamIndex pi = param_index(2, r, 1, TF_W, L + 1);
+  hipLaunchKernelGGL(fused_prep_kernel, dim3((L * 2 * TF_FRAGS + 255) / 256), dim3(256), 0, st, n->params, pi, L, q, B,
+                     r, ws.frags, ws.c);
+  FusedArgs a{};
+  a.params = n->params;
+  a.pi = pi;
+  a.frags = ws.frags;
+  a.x = x;
+  a.c = ws.c;
+  a.u = dg_in ? nullptr : u;
+  a.dg_in = dg_in;
+  a.P = P;
+  a.r = r;
+  a.chunks = row_chunks(P, B);
+  a.chunk_rows = (int)((P + a.chunks - 1) / a.chunks);
+  a.items = (int64_t)B * a.chunks;
+  a.n = (float)((int64_t)B * P);
+  a.part = ws.part;
+  a.spart = ws.cpart;
+  a.opart = ws.mpart;
+  const int wgs = (int)(a.items < TF_MAX_WG ? a.items : TF_MAX_WG);
+  auto k = fused_train_kernel<L>;
+  crom_status s = set_lds(k, (int)sizeof(FusedLds<L>));
+  if (s != CROM_OK) return s;
+  hipLaunchKernelGGL(k, dim3(wgs), dim3(TF_THREADS), sizeof(FusedLds<L>), st, a);
+  FusedReduceArgs f{ws.part, ws.mpart, ws.cpart, wgs, L, a.chunks, pi, grad, dg_in ? nullptr : loss,
+                    (double)((int64_t)B * P), ws.csum, B};
+  hipLaunchKernelGGL(fused_reduce_kernel, dim3(L * TF_MAT / 64 + (TF_W + 2 + 63) / 64 + B * (3 * TF_W / 64)), dim3(256),
+                     0, st, f);
+  hipLaunchKernelGGL(layer1_grad_kernel, dim3((TF_W * (2 + r) + TF_W + B * r + 3) / 4), dim3(256), 0, st, ws.csum, q,
+                     n->params + pi.w[0], B, TF_W, 2, r, grad + pi.w[0], grad + pi.b[0], dq);
+  return hip_check(hipGetLastError(), "fused training pass");
+}
+
 template <class T>
 static crom_status decoder_fwd_bwd(const crom_net* n, const float* x, int B, int64_t P, const float* q,
                                    const float* u, const float* dg_in, float* grad, float* dq, float* loss,
@@ -483,6 +551,13 @@ static crom_status decoder_fwd_bwd(const crom_net* n, const float* x, int B, int
   const float* prm = n->params;
   const bool sine = n->act == CROM_ACT_SINE;  // bfloat16 row kernels only (checked at entry)
   crom_status s = CROM_OK;
+  if constexpr (sizeof(T) == 2) {
+    if (fused_shape(n)) {
+      if (depth == 3) return fused_fwd_bwd<2>(n, x, B, P, q, u, dg_in, grad, dq, loss, ws, st);
+      if (depth == 4) return fused_fwd_bwd<3>(n, x, B, P, q, u, dg_in, grad, dq, loss, ws, st);
+      return fused_fwd_bwd<4>(n, x, B, P, q, u, dg_in, grad, dq, loss, ws, st);
+    }
+  }
   // weights in the GEMM precision
   for (int l = 1; l < depth; ++l)
     hipLaunchKernelGGL((convert_kernel<T>), dim3(grid_for((int64_t)W * W)), dim3(256), 0, st, prm + pi.w[l], ws.wt[l],
@@ -538,11 +613,11 @@ static crom_status decoder_fwd_bwd(const crom_net* n, const float* x, int B, int
   {
     // dWout[o][u] = sum_rows dg[row][o] a[row][u]; dbout[o] = sum dg[row][o]
     // (column sums of a weighted by dg, and of dg itself)
-    colsum<T>(ws.a[depth - 1], W, W, 1, rows, dg, rows, D, 1 + D, ws.cpart, COLSUM_CHUNKS, ws.csum, st);
+    colsum<T>(ws.a[depth - 1], W, W, 1, rows, dg, rows, D, 1 + D, ws.cpart, ws.csum, st);
     // csum[1 + o][u] = dWout[o][u]
     hipLaunchKernelGGL(d2f_kernel, dim3(grid_for((int64_t)D * W)), dim3(256), 0, st, ws.csum + W, grad + pi.w[depth],
                        (int64_t)D * W);
-    colsum<float>(dg, D, D, 1, rows, nullptr, 1, 0, 1, ws.cpart, COLSUM_CHUNKS, ws.csum, st);
+    colsum<float>(dg, D, D, 1, rows, nullptr, 1, 0, 1, ws.cpart, ws.csum, st);
     hipLaunchKernelGGL(d2f_kernel, dim3(1), dim3(64), 0, st, ws.csum, grad + pi.b[depth], (int64_t)D);
     if (sine && D == 1)
       hipLaunchKernelGGL((dz_last_kernel<T, 1, true>), dim3(grid_for(rows * W / 8)), dim3(256), 0, st, dg,
@@ -575,7 +650,7 @@ static crom_status decoder_fwd_bwd(const crom_net* n, const float* x, int B, int
       if ((s = gemm<T, true, false, EPI_NONE>(gw, st)) != CROM_OK) return s;
     }
     // db_l = column sums of dz
-    colsum<T>(dz, W, W, 1, rows, nullptr, 1, 0, 1, ws.cpart, COLSUM_CHUNKS, ws.csum, st);
+    colsum<T>(dz, W, W, 1, rows, nullptr, 1, 0, 1, ws.cpart, ws.csum, st);
     hipLaunchKernelGGL(d2f_kernel, dim3(grid_for(W)), dim3(256), 0, st, ws.csum, grad + pi.b[l], (int64_t)W);
     // dz_{l-1} = (dz W_l) * ELU'(a_{l-1})
     bool done = false;
@@ -607,8 +682,8 @@ static crom_status decoder_fwd_bwd(const crom_net* n, const float* x, int B, int
   // ---- first layer: per-snapshot sums of dz1 and of dz1 * x_i ----
   {
     const int nw = 1 + m;
-    colsum<T>(dz, W, W, B, P, x, P, m, nw, ws.cpart, COLSUM_CHUNKS, ws.csum, st);
-    hipLaunchKernelGGL(layer1_grad_kernel, dim3(grid_for((int64_t)W * (m + r) + W + B * r)), dim3(256), 0, st,
+    colsum<T>(dz, W, W, B, P, x, P, m, nw, ws.cpart, ws.csum, st);
+    hipLaunchKernelGGL(layer1_grad_kernel, dim3((W * (m + r) + W + B * r + 3) / 4), dim3(256), 0, st,
                        ws.csum, q, prm + pi.w[0], B, W, m, r, grad + pi.w[0], grad + pi.b[0], dq);
   }
   return hip_check(hipGetLastError(), "decoder backward");
@@ -683,7 +758,7 @@ static crom_status encoder_bwd(const crom_encoder* e, int B, const float* dq, fl
     g.C = grad + pi.w[1];
     g.ldc = e->hidden;
     if ((s = gemm<float, true, false, EPI_NONE>(g, st)) != CROM_OK) return s;
-    colsum<float>(dq, e->r, e->r, 1, B, nullptr, 1, 0, 1, ws.cpart, COLSUM_CHUNKS, ws.csum, st);
+    colsum<float>(dq, e->r, e->r, 1, B, nullptr, 1, 0, 1, ws.cpart, ws.csum, st);
     hipLaunchKernelGGL(d2f_kernel, dim3(1), dim3(64), 0, st, ws.csum, grad + pi.b[1], (int64_t)e->r);
   }
   // dz1 = (dq E2) * ELU'(h)  [B][hidden]
@@ -703,7 +778,7 @@ static crom_status encoder_bwd(const crom_encoder* e, int B, const float* dq, fl
     g.C = grad + pi.w[0];
     g.ldc = e->n_in;
     if ((s = gemm<T, true, false, EPI_NONE>(g, st)) != CROM_OK) return s;
-    colsum<float>(ws.h32, e->hidden, e->hidden, 1, B, nullptr, 1, 0, 1, ws.cpart, COLSUM_CHUNKS, ws.csum, st);
+    colsum<float>(ws.h32, e->hidden, e->hidden, 1, B, nullptr, 1, 0, 1, ws.cpart, ws.csum, st);
     hipLaunchKernelGGL(d2f_kernel, dim3(grid_for(e->hidden)), dim3(256), 0, st, ws.csum, grad + pi.b[0],
                        (int64_t)e->hidden);
   }
