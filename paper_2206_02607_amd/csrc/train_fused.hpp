@@ -7,9 +7,10 @@
 // 0.82 ms for 16 snapshots of 16,384 points.  Here a workgroup carries 128
 // rows through all layers and back with the activations in LDS and every
 // weight gradient in accumulators, so that memory sees the points, the
-// snapshots and one partial gradient per workgroup: MEASURED.
-// What bounds it now is vector work (the ELU and its slope, the bfloat16
-// conversions: about 27 k of the 35 k cycles a block takes), then LDS.
+// snapshots and one partial gradient per workgroup: 215 us for the same pass.
+// Of the 62 k cycles a block of rows takes, vector instructions (the ELU and
+// its slope, the bfloat16 conversions) are issued in about 25 k, products in
+// 13 k and LDS is busy in 24 k; the rest waits, at 16 barriers and for LDS.
 //
 // Split.  Eight waves, two per SIMD, so that one wave's products meet the
 // other's epilogue.  In a layer's product a wave takes 32 output units of 64
@@ -19,8 +20,8 @@
 // accumulators per layer; the bias gradient is a product with ones.
 // LDS holds as many 128-row tiles as there are products in one direction:
 // the last layer's activations stay in registers, dz_l takes the place of
-// a_l, and a_0 is computed again for the first weight gradient (a fifth tile
-// would not fit).
+// a_l, and a_0, whose place dz_L takes (a fifth tile would not fit), waits in
+// memory and comes back while the upper layers' gradients are formed.
 //
 // The operands, the K order of every product, the epilogues, the output
 // layer's sum (unit order) and the sums of dz_0 (16 row groups per chunk, in
@@ -34,7 +35,7 @@
 
 namespace crom {
 
-constexpr int TF_W = 128, TF_ROWS = 128, TF_LD = TF_W + 8;  // LDS row: 4 banks further on than the one before
+constexpr int TF_W = 128, TF_ROWS = 128, TF_LD = TF_W + 16;  // LDS row: 8 banks further on than the one before
 constexpr int TF_THREADS = 512, TF_MAX_WG = 256;            // one workgroup per compute unit
 constexpr int TF_FRAGS = (TF_W / 16) * (TF_W / 32) * 64;    // 16-byte fragments of one weight matrix
 constexpr int TF_MAT = TF_W * TF_W + TF_W;                  // a layer's partial gradient: dW, then db
@@ -48,16 +49,20 @@ struct FusedArgs {
   const float* u;       // [B][P] snapshots, or NULL:
   const float* dg_in;   // [B][P] the caller's cotangent
   int64_t P;
-  int r, chunks, chunk_rows;  // per snapshot, as colsum splits its rows
+  int64_t chunk_rows;         // of a snapshot's rows, as colsum splits them
+  int r, chunks;
   int64_t items;              // B * chunks
   float n;                    // B * P
   float* part;                // [workgroups][layers][TF_MAT]
+  f32x4* carry;               // [workgroups][3][TF_THREADS]: a chunk's sums of dz_0 between its blocks
+  __bf16* a0;                 // [workgroups][TF_ROWS][TF_LD]: a_0 of the block, as it lies in LDS
   double* spart;              // [items][3][W]: sums of dz_0, dz_0 x_0, dz_0 x_1
   double* opart;              // [workgroups][2 W + 2]: dWout (two halves of the rows), dbout, sum of squares
 };
 
 // Weight fragments of every hidden-to-hidden layer (bfloat16, forward and
-// transposed) and the per-snapshot fold of the first layer
+// transposed; the rows of a pair of M-tiles are dealt so that a lane ends
+// with 8 consecutive units: one 16-byte LDS access) and the per-snapshot fold of the first layer
 // c[b][u] = b1[u] + sum_k W1[u][2 + k] q[b][k] (FP64 accumulation).
 __global__ __launch_bounds__(256) void fused_prep_kernel(const float* __restrict__ params, ParamIndex pi, int L,
                                                          const float* __restrict__ q, int B, int r,
@@ -68,7 +73,7 @@ __global__ __launch_bounds__(256) void fused_prep_kernel(const float* __restrict
     if (f < nf) {
       const int l = f & 63, kb = (f >> 6) % KB, mt = (f >> 6) / KB % (TF_W / 16), dir = f / TF_FRAGS % 2;
       const float* Wl = params + pi.w[1 + f / (2 * TF_FRAGS)];
-      const int m = 16 * mt + (l & 15), k = 32 * kb + 8 * (l >> 4);
+      const int m = 32 * (mt >> 1) + 8 * (l >> 2 & 3) + 4 * (mt & 1) + (l & 3), k = 32 * kb + 8 * (l >> 4);
       bf16x8 v;
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = (__bf16)(dir ? Wl[(k + e) * TF_W + m] : Wl[m * TF_W + k + e]);
@@ -83,11 +88,25 @@ __global__ __launch_bounds__(256) void fused_prep_kernel(const float* __restrict
   }
 }
 
+// Sum over the 16 lanes of a DPP row, in every lane (rotations by 8, 4, 2, 1).
+__device__ __forceinline__ float row16_sum(float v) {
+  auto rot = [](float x, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, false));
+  };
+  v += rot(v, std::integral_constant<int, 0x128>{});
+  v += rot(v, std::integral_constant<int, 0x124>{});
+  v += rot(v, std::integral_constant<int, 0x122>{});
+  v += rot(v, std::integral_constant<int, 0x121>{});
+  return v;
+}
+
 template <int L>
 struct FusedLds {
   __bf16 X[L][TF_ROWS * TF_LD];
-  float wx[2][TF_W], c[TF_W], bias[L][TF_W], wo[TF_W], xs[2][TF_ROWS], dg[TF_ROWS];
-  double red[2][2];
+  float wx[2][TF_W], c[TF_W], bias[L][TF_W], wo[TF_W], xs[2][TF_ROWS];
+  float dg[TF_ROWS];          // the block's snapshot values (or cotangents), then dL/dg
+  double dwo[2][TF_W];        // dWout, two halves of the rows
+  double loss[TF_ROWS][2];    // per row of a block: sums of dL/dg and of the squared errors
 };
 
 template <int L>
@@ -109,9 +128,10 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
   }
   const float bout = a.params[a.pi.b[L + 1]];
 
+  if (tid < TF_ROWS) s.loss[tid][0] = s.loss[tid][1] = 0.0;
+  if (tid < 2 * TF_W) (&s.dwo[0][0])[tid] = 0.0;
+
   f32x4 dw[L][4][2], db[L];
-  float dwo[2][4];
-  double sq = 0.0, sdg = 0.0;
 #pragma unroll
   for (int l = 0; l < L; ++l) {
     db[l] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -120,10 +140,6 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
       for (int j = 0; j < 2; ++j) dw[l][i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) dwo[i][v] = 0.0f;
 
   // Tile `slot` of the activations, its offset formed where it is used: the
   // compiler would otherwise keep every slot's per-lane addresses in
@@ -135,29 +151,39 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
   };
   bf16x8 A[2][KB];  // this wave's weight fragments of the coming product
   const int fo = 2 * wm * KB * 64 + lane;
-  auto load_a = [&](int l, int dir) {
+  auto frags = [&](int l, int dir) {
     int o = (l * 2 + dir) * TF_FRAGS;
     asm volatile("" : "+s"(o));
-    const bf16x8* f = a.frags + o + fo;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb) A[i][kb] = f[(i * KB + kb) * 64];
+    return a.frags + o + fo;
   };
-  auto product = [&](const __bf16* X, f32x4 (&acc)[2][4]) {
+  auto load_a = [&](const bf16x8* f, int kb) {
 #pragma unroll
-    for (int n = 0; n < 4; ++n) {
-      acc[0][n] = acc[1][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int i = 0; i < 2; ++i) A[i][kb] = f[(i * KB + kb) * 64];
+  };
+  // acc = A X over the wave's rows; each K-block's fragments are replaced by
+  // the next product's (NEXT) as soon as they have been used, so that their
+  // loads have this product, its epilogue and a barrier to arrive
+  auto product = [&](auto next, const __bf16* X, f32x4 (&acc)[2][4], int nl, int ndir) {
+    const __bf16* p = X + (64 * wn + lr) * TF_LD + 8 * lg;
+    const bf16x8* f = nullptr;
+    if constexpr (decltype(next)::value) f = frags(nl, ndir);
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) {
-        const bf16x8 b = *reinterpret_cast<const bf16x8*>(&X[(64 * wn + 16 * n + lr) * TF_LD + 32 * kb + 8 * lg]);
+    for (int n = 0; n < 4; ++n) acc[0][n] = acc[1][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(&p[16 * n * TF_LD + 32 * kb]);
 #pragma unroll
         for (int i = 0; i < 2; ++i) acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i][kb], b, acc[i][n], 0, 0, 0);
       }
+      if constexpr (decltype(next)::value) load_a(f, kb);
     }
+    __builtin_amdgcn_sched_barrier(0);
   };
-  // this lane's 4 consecutive units of M-tile 2 wm + i in its row of N-tile n
-  auto at = [&](int i, int n) { return (64 * wn + 16 * n + lr) * TF_LD + 16 * (2 * wm + i) + 4 * lg; };
+  // this lane's 8 consecutive units (4 i + v of its two M-tiles) in its row of N-tile n
+  const int u8 = 32 * wm + 8 * lg;
+  auto at = [&](int n) { return (64 * wn + 16 * n + lr) * TF_LD + u8; };
   // fragment of 16 columns from c0 of rows 32 kk ..: lane (lg, lr) receives rows 8 lg .. 8 lg + 7 of column c0 + lr
   typedef short s16x4 __attribute__((ext_vector_type(4)));
   typedef short s16x8 __attribute__((ext_vector_type(8)));
@@ -186,12 +212,21 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       b = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zb, __builtin_bit_cast(bf16x8, ones_bits), b, 0, 0, 0);
     }
   };
+  // the thread's index, opaque: the addresses formed from it are computed in
+  // the phase that uses them instead of being kept (spilled) across the loop
+  auto self = [&]() {
+    int t = tid;
+    asm volatile("" : "+v"(t));
+    return t;
+  };
   auto elu = [](float z) { return z > 0.0f ? z : __expf(z) - 1.0f; };
-  // a_0 of the block, 8 units of a row per step
+  // a_0 of the block, 8 units of a row per step, and its copy in memory
+  __bf16* a0 = a.a0 + (size_t)blockIdx.x * TF_ROWS * TF_LD;
   auto first_layer = [&]() {
+    const int me = self();
 #pragma unroll
     for (int t = 0; t < TF_ROWS * TF_W / 8 / TF_THREADS; ++t) {
-      const int row = t * (TF_THREADS / 16) + (tid >> 4), u0 = (tid & 15) * 8;
+      const int row = t * (TF_THREADS / 16) + (me >> 4), u0 = (me & 15) * 8;
       const float x0 = s.xs[0][row], x1 = s.xs[1][row];
       bf16x8 o;
 #pragma unroll
@@ -202,98 +237,138 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         o[e] = (__bf16)elu(z);
       }
       *reinterpret_cast<bf16x8*>(&s.X[0][row * TF_LD + u0]) = o;
+      *reinterpret_cast<bf16x8*>(&a0[row * TF_LD + u0]) = o;
     }
   };
+  // ... and back into tile 0, straight to LDS: a wave's load fills 1 KB in lane order
+  auto reload_a0 = [&]() {
+    constexpr int STEP = 64 * 8, LOADS = TF_ROWS * TF_LD / STEP;
+    static_assert(LOADS * STEP == TF_ROWS * TF_LD, "whole wave loads");
+    const int w = __builtin_amdgcn_readfirstlane(wave), me = self() & 63;
+    for (int i = w; i < LOADS; i += TF_THREADS / 64)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(a0 + i * STEP + 8 * me),
+                                       (__attribute__((address_space(3))) void*)(&s.X[0][i * STEP]), 16, 0, 0);
+  };
 
-  for (int64_t item = blockIdx.x; item < a.items; item += gridDim.x) {
-    const int64_t b = item / a.chunks, ch = item - b * a.chunks;
-    const int64_t p0 = ch * a.chunk_rows;
-    const int64_t p1 = p0 + a.chunk_rows < a.P ? p0 + a.chunk_rows : a.P;
-    // a chunk past the last row (the rounded chunk size may leave one) sums nothing
-    float sum[3][4];  // of dz_0 and dz_0 x_k over rows rg, rg + 16, ..., units 4 cv ..
-    const int cv = tid & 31, rg = tid >> 5;
+  // the block's points and snapshot values (rows past the chunk repeat its
+  // last one and carry dz = 0) and its snapshot's fold, loaded a block ahead
+  int64_t item = blockIdx.x, b, p0, p1, r0;  // the grid has at most `items` workgroups
+  float in0, in1 = 0.0f, in2 = 0.0f;
+  auto chunk = [&]() {
+    b = item / a.chunks;
+    p0 = (item - b * a.chunks) * a.chunk_rows;
+    p1 = p0 + a.chunk_rows < a.P ? p0 + a.chunk_rows : a.P;
+    r0 = p0;
+  };
+  auto fetch = [&]() {
+    const int me = self();
+    if (me < TF_ROWS) {
+      const int64_t p = r0 + me < p1 ? r0 + me : p1 - 1;
+      in0 = a.x[2 * p];
+      in1 = a.x[2 * p + 1];
+      in2 = (a.u ? a.u : a.dg_in)[b * a.P + p];
+    } else if (me < TF_ROWS + TF_W) {
+      in0 = a.c[b * TF_W + me - TF_ROWS];
+    }
+  };
+  auto place = [&]() {
+    const int me = self();
+    if (me < TF_ROWS) {
+      s.xs[0][me] = in0;
+      s.xs[1][me] = in1;
+      s.dg[me] = in2;
+    } else if (me < TF_ROWS + TF_W) {
+      s.c[me - TF_ROWS] = in0;
+    }
+  };
+  chunk();
+  fetch();
+  place();
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sum[k][e] = 0.0f;
-    for (int64_t r0 = p0; r0 < p1; r0 += TF_ROWS) {
+  for (int kb = 0; kb < KB; ++kb) load_a(frags(0, 0), kb);
+  __syncthreads();
+
+  while (true) {
       const int valid = p1 - r0 < TF_ROWS ? (int)(p1 - r0) : TF_ROWS;
-      // rows past the chunk repeat its last one and carry dz = 0
-      if (tid < TF_ROWS) {
-        const int64_t p = r0 + (tid < valid ? tid : valid - 1);
-        s.xs[0][tid] = a.x[2 * p];
-        s.xs[1][tid] = a.x[2 * p + 1];
-      } else if (tid < TF_ROWS + TF_W) {
-        s.c[tid - TF_ROWS] = a.c[b * TF_W + tid - TF_ROWS];
-      }
-      load_a(0, 0);
-      __syncthreads();
       first_layer();
       __syncthreads();
 
       // ---- forward
-      uint2 top[2][4];  // a_L at this lane's entries
+      bf16x8 top[4];  // a_L at this lane's entries
 #pragma unroll
       for (int l = 1; l <= L; ++l) {
         f32x4 acc[2][4];
-        product(tile(l - 1), acc);
-        load_a(l < L ? l : L - 1, l < L ? 0 : 1);
+        product(std::true_type{}, tile(l - 1), acc, l < L ? l : L - 1, l < L ? 0 : 1);
         __bf16* out = tile(l < L ? l : 0);
+        const f32x4 bv[2] = {*reinterpret_cast<const f32x4*>(&s.bias[l - 1][u8]),
+                             *reinterpret_cast<const f32x4*>(&s.bias[l - 1][u8 + 4])};
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const f32x4 bv = *reinterpret_cast<const f32x4*>(&s.bias[l - 1][16 * (2 * wm + i) + 4 * lg]);
+        for (int n = 0; n < 4; ++n) {
+          bf16x8 o;
 #pragma unroll
-          for (int n = 0; n < 4; ++n) {
-            bf16x4 o;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) o[v] = (__bf16)elu(acc[i][n][v] + bv[v]);
-            *reinterpret_cast<bf16x4*>(&out[at(i, n)]) = o;
-            if (l == L) top[i][n] = __builtin_bit_cast(uint2, o);
-          }
+          for (int e = 0; e < 8; ++e) o[e] = (__bf16)elu(acc[e >> 2][n][e & 3] + bv[e >> 2][e & 3]);
+          *reinterpret_cast<bf16x8*>(&out[at(n)]) = o;
+          if (l == L) top[n] = o;
         }
         __syncthreads();
       }
 
       // ---- output layer and dL/dg, one thread per row, in unit order
       if (tid < TF_ROWS) {
-        float d = 0.0f;
-        if (tid < valid) {
-          const int64_t row = b * a.P + r0 + tid;
-          if (a.u) {
-            float g = 0.0f;
-#pragma unroll 4
-            for (int u0 = 0; u0 < TF_W; u0 += 8) {
-              const bf16x8 v = *reinterpret_cast<const bf16x8*>(&s.X[0][tid * TF_LD + u0]);
+        const int row = self();
+        float d = s.dg[row];
+        double e2 = 0.0;
+        if (a.u) {
+          float g = 0.0f;
+          const __bf16* X = tile(0) + row * TF_LD;
+          // uniform addresses: scalar loads, operands of the products
+          const __attribute__((address_space(4))) float* wo =
+              (const __attribute__((address_space(4))) float*)(a.params + a.pi.w[L + 1]);
 #pragma unroll
-              for (int e = 0; e < 8; ++e) g += s.wo[u0 + e] * (float)v[e];
-            }
-            const float e = (g + bout) - a.u[row];
-            d = 2.0f * e / a.n;
-            sq += (double)e * e;
-          } else {
-            d = a.dg_in[row];
+          for (int h = 0; h < TF_W; h += 64) {
+            bf16x8 v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const bf16x8*>(&X[h + 8 * i]);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+              for (int e = 0; e < 8; ++e) g += wo[h + 8 * i + e] * (float)v[i][e];
           }
-          sdg += (double)d;
+          const float e = (g + bout) - d;
+          d = 2.0f * e / a.n;
+          e2 = (double)e * e;
         }
-        s.dg[tid] = d;
+        if (row >= valid) d = 0.0f;
+        s.dg[row] = d;
+        s.loss[row][0] += (double)d;
+        if (row < valid) s.loss[row][1] += e2;
       }
       __syncthreads();
+      {
+        __bf16* Z = tile(0);
+        const int me = self(), half = me >> 8, u0 = 32 * (me >> 6 & 3) + 8 * (me >> 4 & 3), row0 = 64 * half + (me & 15);
+        float dwo[8];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const f32x4 wv = *reinterpret_cast<const f32x4*>(&s.wo[16 * (2 * wm + i) + 4 * lg]);
+        for (int e = 0; e < 8; ++e) dwo[e] = 0.0f;
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
-          const int row = 64 * wn + 16 * n + lr;
+          const int row = row0 + 16 * n;
           const float d = s.dg[row];
-          const bf16x4 av = __builtin_bit_cast(bf16x4, top[i][n]);
-          bf16x4 o;
+          bf16x8 o;
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const float t = d * wv[v];
-            o[v] = (__bf16)(row < valid ? t * elu_d1_from_a((float)av[v]) : 0.0f);
-            dwo[i][v] += d * (float)av[v];
+          for (int e = 0; e < 8; ++e) {
+            const float t = d * s.wo[u0 + e], av = (float)top[n][e];
+            o[e] = (__bf16)(t * elu_d1_from_a(av));
+            dwo[e] += d * av;
           }
-          *reinterpret_cast<bf16x4*>(&s.X[0][at(i, n)]) = o;
+          uint4 bits = __builtin_bit_cast(uint4, o);
+          if (row >= valid) bits = uint4{0, 0, 0, 0};
+          *reinterpret_cast<uint4*>(&Z[row * TF_LD + u0]) = bits;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          dwo[e] = row16_sum(dwo[e]);
+          if ((me & 15) == 0) s.dwo[half][u0 + e] += (double)dwo[e];
         }
       }
       __syncthreads();
@@ -304,59 +379,77 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         const __bf16* Z = tile(l == L ? 0 : l);
         __bf16* G = tile(l - 1);
         f32x4 acc[2][4];
-        product(Z, acc);
-        if (l > 1) load_a(l - 2, 1);
-        uint2 o[2][4];
+        // after the last product: the next block's first
+        product(std::true_type{}, Z, acc, l > 1 ? l - 2 : 0, l > 1 ? 1 : 0);
+        bf16x8 o[4];
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int n = 0; n < 4; ++n) {
+          const bf16x8 gv = *reinterpret_cast<const bf16x8*>(&G[at(n)]);
 #pragma unroll
-          for (int n = 0; n < 4; ++n) {
-            const bf16x4 gv = *reinterpret_cast<const bf16x4*>(&G[at(i, n)]);
-            bf16x4 t;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) t[v] = (__bf16)(acc[i][n][v] * elu_d1_from_a((float)gv[v]));
-            o[i][n] = __builtin_bit_cast(uint2, t);
-          }
+          for (int e = 0; e < 8; ++e) o[n][e] = (__bf16)(acc[e >> 2][n][e & 3] * elu_d1_from_a((float)gv[e]));
+        }
         weight_grad(Z, G, dw[l - 1], db[l - 1]);
         __syncthreads();  // dz_l and a_{l-1} have been read
+        if (l == L) reload_a0();  // where dz_L was
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int n = 0; n < 4; ++n) *reinterpret_cast<uint2*>(&G[at(i, n)]) = o[i][n];
-        if (l == 2) first_layer();  // a_0 again, where dz_L was
+        for (int n = 0; n < 4; ++n) *reinterpret_cast<bf16x8*>(&G[at(n)]) = o[n];
+        if (l == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // a_0 has arrived
         __syncthreads();
       }
 
-      // ---- sums of dz_0 over the block, continuing the chunk's
+      // ---- sums of dz_0 and dz_0 x_k over the block, continuing the chunk's;
+      // the next block's inputs meanwhile
+      f32x4 sum[3];
+      const int me = self(), cv = me & 31, rg = me >> 5;  // rows rg, rg + 16, ..., units 4 cv ..
+      f32x4* carry = a.carry + (size_t)blockIdx.x * 3 * TF_THREADS + me;
 #pragma unroll
-      for (int t = 0; t < TF_ROWS / 16; ++t) {
-        const int row = rg + 16 * t;
-        const bf16x4 z = *reinterpret_cast<const bf16x4*>(&s.X[0][row * TF_LD + 4 * cv]);
-        const float x0 = s.xs[0][row], x1 = s.xs[1][row];
+      for (int k = 0; k < 3; ++k) sum[k] = r0 > p0 ? carry[k * TF_THREADS] : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      const int64_t done = item;
+      bool more = true;
+      r0 += TF_ROWS;
+      const bool last = r0 >= p1;  // of its chunk
+      if (last) {
+        item += gridDim.x;
+        more = item < a.items;
+        if (more) chunk();
+      }
+      if (more) fetch();
+      {
+        const __bf16* X = tile(0) + 4 * cv;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float v = (float)z[e];
-          sum[0][e] += v;
-          sum[1][e] += v * x0;
-          sum[2][e] += v * x1;
+        for (int t = 0; t < TF_ROWS / 16; ++t) {
+          const int row = rg + 16 * t;
+          const bf16x4 z = *reinterpret_cast<const bf16x4*>(&X[row * TF_LD]);
+          const float x0 = s.xs[0][row], x1 = s.xs[1][row];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float v = (float)z[e];
+            sum[0][e] += v;
+            sum[1][e] += v * x0;
+            sum[2][e] += v * x1;
+          }
         }
       }
-      __syncthreads();  // before the next block's points
-    }
-    // the chunk's 16 row groups in order (X[1] is free until the next block's second layer)
-    float* sh = reinterpret_cast<float*>(s.X[1]);  // [3][16][W]
+      if (last) {  // the chunk's 16 row groups in order, through a tile that is free here
+        float* sh = reinterpret_cast<float*>(tile(1));  // [3][16][W]
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
-      *reinterpret_cast<f32x4*>(&sh[(k * 16 + rg) * TF_W + 4 * cv]) = f32x4{sum[k][0], sum[k][1], sum[k][2], sum[k][3]};
-    __syncthreads();
-    if (tid < 3 * TF_W) {
-      const int k = tid / TF_W, col = tid % TF_W;
-      double t = 0.0;
+        for (int k = 0; k < 3; ++k) *reinterpret_cast<f32x4*>(&sh[(k * 16 + rg) * TF_W + 4 * cv]) = sum[k];
+        __syncthreads();
+        if (tid < 3 * TF_W) {
+          const int k = me / TF_W, col = me % TF_W;
+          double t = 0.0;
 #pragma unroll
-      for (int g = 0; g < 16; ++g) t += (double)sh[(k * 16 + g) * TF_W + col];
-      a.spart[item * 3 * TF_W + tid] = t;
-    }
-    __syncthreads();
+          for (int g = 0; g < 16; ++g) t += (double)sh[(k * 16 + g) * TF_W + col];
+          a.spart[done * 3 * TF_W + me] = t;
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) carry[k * TF_THREADS] = sum[k];
+        __syncthreads();
+      }
+      if (!more) break;
+      place();
+      __syncthreads();
   }
 
   // ---- this workgroup's partial gradients
@@ -376,28 +469,16 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     }
   }
   double* op = a.opart + (size_t)blockIdx.x * (2 * TF_W + 2);
+  if (tid < 2 * TF_W) op[tid] = (&s.dwo[0][0])[tid];
+  if (wave == 0) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int k = 0; k < 2; ++k) {
+      double t = s.loss[lane][k] + s.loss[lane + 64][k];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      double t = (double)dwo[i][v];
-#pragma unroll
-      for (int m = 1; m < 16; m <<= 1) t += __shfl_xor(t, m);
-      if (lr == 0) op[wn * TF_W + 16 * (2 * wm + i) + 4 * lg + v] = t;
-    }
-  if (wave < 2) {
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-      sdg += __shfl_xor(sdg, m);
-      sq += __shfl_xor(sq, m);
-    }
-    if (lane == 0) {
-      s.red[wave][0] = sdg;
-      s.red[wave][1] = sq;
+      for (int m = 1; m < 64; m <<= 1) t += __shfl_xor(t, m);
+      if (lane == 0) op[2 * TF_W + k] = t;
     }
   }
-  __syncthreads();
-  if (tid < 2) op[2 * TF_W + tid] = s.red[0][tid] + s.red[1][tid];
 }
 
 // Sums the workgroups' partials in order (4 interleaved lanes per output,

@@ -502,3 +502,39 @@ def test_train_state_checkpoint_resume(cuda, prec):
     nd = D.params.numel()
     assert torch.equal(T.state[lay.dec_params:lay.dec_params + 4 * nd].view(torch.float32), D.params)
     assert lay.total == len(T.state) and lay.dec_params == 0
+
+
+# the fused decoder pass (width 128, bfloat16, 3 to 5 hidden layers): one row,
+# the edges of its 128-row blocks and 256-row chunks, several chunks per
+# workgroup, both latent sizes; depths 2 and 6 take the layerwise kernels
+@pytest.mark.parametrize("depth,r,B,P", [(5, 8, 1, 1), (5, 8, 2, 127), (3, 8, 2, 128), (4, 8, 1, 129), (5, 8, 3, 257),
+                                         (5, 16, 2, 385), (3, 8, 300, 260), (2, 8, 2, 129), (6, 8, 2, 129)])
+def test_fused_pass_edges(cuda, depth, r, B, P):
+    import torch
+    from paper_2206_02607_amd import crom
+    g = rng(100 * depth + P)
+    dec = xavier_mlp(g, 2, r, 1, 128, depth, bias_scale=0.2)
+    enc = xavier_mlp(g, P, 0, r, 24, 1, bias_scale=0.2)
+    x = uniform_points(g, P, 2)
+    u = g.uniform(-1, 1, size=(B, P)).astype(np.float32)
+    D, T = _trainer(dec, enc, x, u, 2, "bf16", cuda, hidden=24)
+    loss, gd, ge, q = T.grads(torch.from_numpy(u).to(cuda))
+    rl, rgd, rge, rq = train.loss_and_grads(*_as_held(dec, enc, "bf16"), x, u)
+    # the loss is a mean square: the tolerance bounds the values' error, so the
+    # root moves by at most that (one row averages nothing)
+    errs = {"rms": abs(loss.item() ** 0.5 - rl ** 0.5) / max(rl ** 0.5, np.abs(u).max()),
+            "q": normwise_rel(q.cpu().numpy(), rq)}
+    for name, got, ref, layers in (("dec", gd, rgd, dec), ("enc", ge, rge, enc)):
+        for li, ((gW, gb), (rW, rb)) in enumerate(zip(_split(got.cpu().numpy(), layers), ref)):
+            errs[f"{name}W{li}"] = normwise_rel(gW, rW)
+            errs[f"{name}b{li}"] = normwise_rel(gb, rb)
+    # the cotangent of the loss through the vector-Jacobian product (other chunks, no loss)
+    qn = q.clone()
+    G = torch.empty(B, P, 1, device=cuda)
+    for b in range(B):
+        D.decode(torch.from_numpy(x).to(cuda), qn[b].double(), out=G[b])
+    dg = 2 * (G[..., 0] - torch.from_numpy(u).to(cuda)) / (B * P)
+    gp, gq = crom.decode_vjp(D, torch.from_numpy(x).to(cuda), qn, dg.reshape(B, P, 1))
+    errs["vjp"] = normwise_rel(gp.cpu().numpy(), gd.cpu().numpy())
+    bad = {k: v for k, v in errs.items() if not v <= TOL["bf16"]}
+    assert not bad, bad
