@@ -196,6 +196,79 @@ static crom_status launch_decode(const DecodeArgs& a, hipStream_t st) {
   }
 }
 
+// FP32 with the latent Jacobian by the reverse pass (RevJets): the forward
+// columns CF and one adjoint column per output, where forward tangents take
+// one column per latent value (2D: 4 + 1 columns instead of 12; at width 256
+// 4 + 3 or 5 + 3 instead of 20 more).  FP32-matrix-core-bound either way:
+// 20,011 points of the 2D decoder with the Laplacian took 273 us by forward
+// tangents and take 116; streamed weight fragments leave room for three
+// workgroups per compute unit (200,000 points: 1.07 ms, 123 TFLOP/s, against
+// 1.14 with a layer's fragments held and two).  The bfloat16 modes keep the
+// forward columns: there the two differ by the bfloat16 rounding of their
+// operands.
+template <class S, class CF, int NW, int PF, int WPE>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) void decode_rev_kernel(DecodeArgs a) {
+  using RJ = RevJets<S, CF, NW, PREC_FP32, PF, false>;
+  using CO = typename RJ::CO;
+  constexpr int D = S::D, M = S::M, R = S::R, NTO = RJ::NTO;
+  extern __shared__ __align__(16) char lds[];
+  float* par = reinterpret_cast<float*>(lds + RJ::LDS_BYTES);
+  const float* res = reinterpret_cast<const float*>(lds + RJ::RES_OFF);
+  RJ::PC::load(par, a.params, a.pi, a.depth, RJ::THREADS);
+  __syncthreads();
+  const int64_t nbatch = (a.P + PT - 1) / PT;
+  for (int64_t bi = blockIdx.x; bi < nbatch; bi += gridDim.x) {
+    const int64_t first = bi * PT;
+    const int n_valid = a.P - first < PT ? (int)(a.P - first) : PT;
+    RJ::stage(lds, a.x, first, n_valid, a.q, nullptr, par);
+    __syncthreads();
+    RJ::run(lds, par, a.packed, a.depth);
+    // the batch's rows of each output array, in memory order
+    for (int i = threadIdx.x; i < n_valid * D * NTO; i += RJ::THREADS) {
+      const int lp = i / (D * NTO), oo = i / NTO % D, c = i % NTO;
+      const int64_t row = (first + lp) * D + oo;
+      const float v = res[(oo * NTO + c) * PT + lp];
+      const int k = CO::kind(c);
+      if (k == CK_VAL) {
+        a.g[row] = v;
+      } else if (k == CK_XT) {
+        if (a.dgdx) a.dgdx[row * M + (c - CO::X0)] = v;
+      } else if (k == CK_LAP) {
+        a.d2g[row] = v;
+      } else if (k == CK_HESS) {
+        a.d2g[row * (M * (M + 1) / 2) + (c - CO::D0)] = v;
+      } else {
+        a.dgdq[row * R + (c - CO::Q0)] = v;
+      }
+    }
+    __syncthreads();  // res is read before the next batch may overwrite the LDS
+  }
+}
+
+// Launches the reverse pass where it is compiled and fits; *done tells.
+template <class S, bool XT, int D2>
+static crom_status decode_rev(const DecodeArgs& a, bool* done, hipStream_t st) {
+  using CF = Cols<S::M, S::R, 1, 0, XT, D2, 0>;
+  constexpr int NW = DecodeTune<S, PREC_FP32>::NW, PF = 2, WPE = S::R <= 8 ? 3 : 2;
+  using RJ = RevJets<S, CF, NW, PREC_FP32, PF, false>;
+  const int lds_bytes = RJ::LDS_BYTES + RJ::PC::bytes(a.depth);
+  *done = RJ::supported(a.depth) && lds_bytes <= LDS_MAX;
+  if (!*done) return CROM_OK;
+  auto k = decode_rev_kernel<S, CF, NW, PF, WPE>;
+  static bool attr = false;
+  if (!attr) {
+    crom_status s = set_lds(k, LDS_MAX);
+    if (s != CROM_OK) return s;
+    attr = true;
+  }
+  const int64_t blocks = (a.P + PT - 1) / PT;
+  if (blocks > 0x7fffffff) return fail(CROM_ERR_INVALID_ARG, "P too large");
+  // one wave of resident workgroups, each loading the parameters once
+  const int64_t cap = 256 * (LDS_MAX / lds_bytes < 3 ? LDS_MAX / lds_bytes : 3);
+  hipLaunchKernelGGL(k, dim3((unsigned)(blocks < cap ? blocks : cap)), dim3(NW * 64), lds_bytes, st, a);
+  return hip_check(hipGetLastError(), "decode launch");
+}
+
 // One pass over the points with a fixed column set (value first).
 template <class S, int NW, int PREC, bool XT, int D2, int NQ, int HB = 0,
           int NH = S::M * (S::M + 1) / 2>
@@ -234,6 +307,24 @@ template <class S, int NW, int PREC, int QC, int HC>
 static crom_status decode_shape(const DecodeArgs& a0, bool xt, int d2, bool qt, hipStream_t st) {
   DecodeArgs a = a0;
   const bool spatial = xt || d2 != D2_NONE;
+  if constexpr (PREC == PREC_FP32) {
+    if (qt) {
+      bool done = false;
+      crom_status s = CROM_OK;
+      if constexpr (S::W <= 128) {
+        if (d2 == D2_LAP) s = decode_rev<S, true, D2_LAP>(a, &done, st);
+        else if (d2 == D2_NONE && xt) s = decode_rev<S, true, D2_NONE>(a, &done, st);
+        else if (d2 == D2_NONE) s = decode_rev<S, false, D2_NONE>(a, &done, st);
+        if constexpr (S::M > 1) {
+          if (d2 == D2_HESS) s = decode_rev<S, true, D2_HESS>(a, &done, st);
+        }
+      } else {  // the adjoint tiles need the x tangents' room; Hessians follow their own passes below
+        if (d2 == D2_LAP) s = decode_rev<S, true, D2_LAP>(a, &done, st);
+        else if (d2 == D2_NONE) s = decode_rev<S, true, D2_NONE>(a, &done, st);
+      }
+      if (done || s != CROM_OK) return s;
+    }
+  }
   if constexpr (S::W <= 128 && S::R <= 8) {
 #define CROM_ONE(XT, D2)                                                                  \
     if (spatial == XT && d2 == D2)                                                        \
@@ -253,6 +344,13 @@ static crom_status decode_shape(const DecodeArgs& a0, bool xt, int d2, bool qt, 
     else if (xt) s = run_pass<S, NW, PREC, true, D2_NONE, 0>(a, st);
     else if (!qt) s = run_pass<S, NW, PREC, false, D2_NONE, 0>(a, st);
     if (s != CROM_OK || !qt) return s;
+    if constexpr (PREC == PREC_FP32 && S::W > 128) {
+      if (d2 == D2_HESS) {
+        bool done = false;
+        s = decode_rev<S, true, D2_NONE>(a, &done, st);
+        if (done || s != CROM_OK) return s;
+      }
+    }
     for (int qb = 0; qb < S::R; qb += QC) {
       a.qb = qb;
       s = run_pass<S, NW, PREC, false, D2_NONE, QC>(a, st);
