@@ -50,6 +50,8 @@
 // instances report CROM_FLAG_ABORTED.
 #include <stddef.h>
 
+#include <algorithm>
+
 #include "common.hpp"
 #include "tune.hpp"
 
@@ -102,6 +104,20 @@
 // spills (three spill 80 registers).
 #ifndef CROM_GN_REV_WPE
 #define CROM_GN_REV_WPE 2
+#endif
+// FP32 evaluations of large batches: streamed weight fragments, three
+// workgroups per compute unit (two with the round kernel's three engines,
+// which three spill) instead of a layer's fragments held and one.  Linearised
+// step of 256 instances 1.71 -> 1.58 ms, Gauss-Newton step of 64 instances
+// 2.01 -> 1.62 ms (three workgroups 1.68).
+#ifndef CROM_F32_PF
+#define CROM_F32_PF 2
+#endif
+#ifndef CROM_F32_LIN_WPE
+#define CROM_F32_LIN_WPE 3
+#endif
+#ifndef CROM_F32_GN_WPE
+#define CROM_F32_GN_WPE 2
 #endif
 
 namespace crom {
@@ -209,7 +225,7 @@ static WsLayout ws_layout(int r, int d, int m, int n_inst, int64_t total) {
   L.state = o;     o = align256(o + sizeof(GNState) * (size_t)n_inst);
   L.jets = o;      o = align256(o + 4 * (size_t)total * L.nj);
   L.work = o;      o = align256(o + 4 * 2 * (size_t)L.nblk_max);  // round kernels: two batch lists
-  L.work_cnt = o;  o = align256(o + 16);
+  L.work_cnt = o;  o = align256(o + 8 * (size_t)(MAXP + 2));  // each round's length
   // elastic step: each batch's Jacobian rows and residuals, assembled from
   // the workgroups of its latent-tangent chunks, and their arrival counts
   const size_t jrows = L.nj ? (size_t)PT * d * (r + TV) : 0;
@@ -371,7 +387,10 @@ __global__ __launch_bounds__(SETUP_THREADS) void setup_kernel(StepArgs a) {
     sync[SYNC_EXITED] = 0;
     act_phase[0] = n_active;
   }
-  for (int p = tid + 1; p < MAXP + 2; p += SETUP_THREADS) act_phase[p] = 0;
+  for (int p = tid + 1; p < MAXP + 2; p += SETUP_THREADS) {
+    act_phase[p] = 0;
+    wsp<uint64_t>(a, a.L.work_cnt)[p] = 0;
+  }
   for (int i = tid; i < a.n_inst; i += SETUP_THREADS) {
     inst_cnt[i] = 0;
     wsp<uint32_t>(a, a.L.inv)[i] = 0;
@@ -1274,6 +1293,13 @@ __device__ __forceinline__ CholOut chol_solve(const double* up, const double* b)
   else return row_chol_solve<R>(up, b);
 }
 
+// The same as a call: its registers then do not add to the caller's (the
+// round kernels, whose evaluations leave none).
+template <int R>
+__device__ __attribute__((noinline)) CholOut chol_solve_call(const double* up, const double* b) {
+  return chol_solve<R>(up, b);
+}
+
 // ---------------------------------------------------------------------------
 // Gauss-Newton control of one instance in phase p, by the workgroup that
 // completed the instance's last batch of the phase.  The workgroup copies
@@ -1287,8 +1313,12 @@ __device__ __forceinline__ CholOut chol_solve(const double* up, const double* b)
 // LAZY: the rounds after a rejected trial evaluated the objective only (no
 // Jacobian), so a trial accepted there is followed by a re-linearisation
 // round; otherwise every round carries J at its first trial.
-template <int R, bool LAZY = false>
-__device__ bool solve_instance(const StepArgs& a, char* lds, int inst, int p, bool is_last) {
+// NTH: the thread count whose summation order the partials take (0: the
+// workgroup's own), so that workgroups of different sizes agree bit for bit.
+// LIST: an instance that goes on appends its batches to the next round's
+// work list (in any order: each batch keeps its own partials slot).
+template <int R, bool LAZY = false, int NTH = 0, bool LIST = false>
+__device__ void solve_instance(const StepArgs& a, char* lds, int inst, int p, bool is_last) {
   constexpr int NA = R * (R + 1) / 2;
   constexpr int NRED = NA + R + TV;
   constexpr int NWORD = sizeof(GNState) / 8;
@@ -1297,7 +1327,7 @@ __device__ bool solve_instance(const StepArgs& a, char* lds, int inst, int p, bo
   GNState* st = reinterpret_cast<GNState*>(lds);
   double* sub = reinterpret_cast<double*>(lds + ((sizeof(GNState) + 15) / 16) * 16);
   const int nth = blockDim.x;
-  const int NS = nth / NRED;  // strided subsets per entry
+  const int NS = (NTH ? NTH : nth) / NRED;  // strided subsets per entry
   double* red = sub + NS * NRED;
   __shared__ int s_done;
   // The state and the batch partials are independent: their loads are all
@@ -1315,8 +1345,8 @@ __device__ bool solve_instance(const StepArgs& a, char* lds, int inst, int p, bo
       reinterpret_cast<uint64_t*>(st)[w] = ld_c(reinterpret_cast<const uint64_t*>(gst) + w);
   }
   const double* part = wsp<double>(a, a.L.partials);
-  if (threadIdx.x < NS * NRED) {
-    const int e = threadIdx.x % NRED, sl = threadIdx.x / NRED;
+  for (int w = threadIdx.x; w < NS * NRED; w += nth) {
+    const int e = w % NRED, sl = w / NRED;
     double acc = 0.0;
     for (int32_t base = b0 + sl; base < b1; base += UNR * NS) {
       double v[UNR];
@@ -1438,7 +1468,7 @@ __device__ bool solve_instance(const StepArgs& a, char* lds, int inst, int p, bo
         flags |= CROM_FLAG_NONFINITE;
         done = true;
       } else {
-        const CholOut o = chol_solve<R>(red, bv);
+        const CholOut o = NTH ? chol_solve_call<R>(red, bv) : chol_solve<R>(red, bv);
         const double xk = lane < R ? o.x : 0.0, dn = o.xx, sl = o.bx;
         double qq = 0.0;
 #pragma unroll
@@ -1530,15 +1560,61 @@ __device__ bool solve_instance(const StepArgs& a, char* lds, int inst, int p, bo
     st_c(wsp<uint32_t>(a, a.L.inst_cnt) + inst, 0u);
     if (!s_done) atomicAdd(reinterpret_cast<unsigned long long*>(wsp<int64_t>(a, a.L.act_phase) + p + 1), 1ull);
   }
+  if constexpr (LIST) {
+    if (s_done == 0) {  // uniform
+      __shared__ int64_t s_base;
+      if (threadIdx.x == 0)
+        s_base = (int64_t)atomicAdd(wsp<unsigned long long>(a, a.L.work_cnt) + p + 1, (unsigned long long)(b1 - b0));
+      __syncthreads();
+      int32_t* next = wsp<int32_t>(a, a.L.work) + (int64_t)((p + 1) % 2) * a.L.nblk_max + s_base;
+      for (int32_t i = threadIdx.x; i < b1 - b0; i += nth) st_c(next + i, b0 + i);
+    }
+  }
   wait_mem();
   __syncthreads();
   if (p == 1) trace_solve(a, 51);
-  const bool cont = s_done == 0;
   if (threadIdx.x == 0)
     atomicAdd(reinterpret_cast<unsigned long long*>(wsp<uint64_t>(a, a.L.sync) + SYNC_SOLVED), 1ull);
   __syncthreads();
   if (p == 1) trace_solve(a, 52);
-  return cont;  // the instance takes part in the next round
+}
+
+// Thread 0: waits until `target` solves are counted (bounded by SPIN_MAX
+// polls; on overrun the abort word is set); returns whether the step aborted.
+constexpr int64_t SPIN_MAX = int64_t(1) << 21;  // bounded waits: ~2e6 polls of ~1 us
+__device__ __forceinline__ bool wait_solved(uint64_t* sync, uint64_t target) {
+  int64_t spins = 0;
+  while (ld_c(sync + SYNC_SOLVED) < target) {
+    if (ld_c(sync + SYNC_ABORT) != 0 || ++spins > SPIN_MAX) {
+      st_c(sync + SYNC_ABORT, (uint64_t)1);
+      break;
+    }
+    __builtin_amdgcn_s_sleep(2);
+  }
+  return ld_c(sync + SYNC_ABORT) != 0;
+}
+
+// The last workgroup to leave marks the instances an abort left unfinished.
+// Every other workgroup has left its loop by then, so no solve runs after
+// this: a solve that completed after the abort word was set either finished
+// its instance (a complete result) or moved it to a phase nobody evaluates,
+// which is marked here.
+__device__ __forceinline__ void leave_rounds(const StepArgs& a) {
+  __shared__ int s_out;
+  uint64_t* sync = wsp<uint64_t>(a, a.L.sync);
+  wait_mem();
+  __syncthreads();
+  if (threadIdx.x == 0)
+    s_out = atomicAdd(reinterpret_cast<unsigned long long*>(sync + SYNC_EXITED), 1ull) + 1 ==
+            (unsigned long long)gridDim.x;
+  __syncthreads();
+  if (s_out && ld_c(sync + SYNC_ABORT) != 0) {
+    const GNState* state = wsp<GNState>(a, a.L.state);
+    for (int i = threadIdx.x; i < a.n_inst; i += blockDim.x) {
+      if (ld_c(&state[i].phase) != PH_DONE)
+        st_c(&a.info[i].flags, ld_c(&a.info[i].flags) | CROM_FLAG_ABORTED);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1549,8 +1625,6 @@ __device__ bool solve_instance(const StepArgs& a, char* lds, int inst, int p, bo
 // hanging.  A plain launch: the cooperative launch API measured 18 us more
 // per step in dispatch.
 // ---------------------------------------------------------------------------
-constexpr int64_t SPIN_MAX = int64_t(1) << 21;  // bounded waits: ~2e6 polls of ~1 us
-
 // Engines and LDS layout of the persistent kernel per PDE kind: the
 // engines' activation regions share the start of the dynamic LDS; the
 // elastic kind keeps its J rows and residuals (FP64) above them; the
@@ -1684,38 +1758,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
     }
     trace_mark(a, 4 * p + 1);
     // wait until every instance active in this phase has been solved
-    if (threadIdx.x == 0) {
-      int64_t spins = 0;
-      while (ld_c(sync + SYNC_SOLVED) < target) {
-        if (ld_c(sync + SYNC_ABORT) != 0 || ++spins > SPIN_MAX) {
-          st_c(sync + SYNC_ABORT, (uint64_t)1);
-          break;
-        }
-        __builtin_amdgcn_s_sleep(2);
-      }
-      s_abort = ld_c(sync + SYNC_ABORT) != 0;
-    }
+    if (threadIdx.x == 0) s_abort = wait_solved(sync, target);
     __syncthreads();
     aborted = s_abort != 0;
     trace_mark(a, 4 * p + 2);
   }
-  // The last workgroup to leave marks the instances an abort left
-  // unfinished.  Every other workgroup has left its loop by then, so no
-  // solve runs after this: a solve that completed after the abort word was
-  // set either finished its instance (a complete result) or moved it to a
-  // phase nobody evaluates, which is marked here.
-  wait_mem();
-  __syncthreads();
-  if (threadIdx.x == 0)
-    s_last = atomicAdd(reinterpret_cast<unsigned long long*>(sync + SYNC_EXITED), 1ull) + 1 ==
-             (unsigned long long)gridDim.x;
-  __syncthreads();
-  if (s_last && ld_c(sync + SYNC_ABORT) != 0) {
-    for (int i = threadIdx.x; i < a.n_inst; i += blockDim.x) {
-      if (ld_c(&state[i].phase) != PH_DONE)
-        st_c(&a.info[i].flags, ld_c(&a.info[i].flags) | CROM_FLAG_ABORTED);
-    }
-  }
+  leave_rounds(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -1896,13 +1944,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
   __shared__ int s_ph, s_lt;
   __shared__ double qdl[TV * RMAX];
   // Round p >= 1 evaluates the batches that the solves of round p - 1 listed
-  // for their continuing instances (list p % 2); this round's solves fill
-  // the other list, whose count is cleared here (the solves run after this
-  // kernel on the same stream).  Round 0 evaluates every batch.
-  int64_t* work_cnt = wsp<int64_t>(a, a.L.work_cnt);
-  if (blockIdx.x == 0 && threadIdx.x == 0) work_cnt[(p + 1) % 2] = 0;
+  // for their continuing instances (list p % 2, a count per round); this
+  // round's solves fill the other list.  Round 0 evaluates every batch.
   if (ld_c(wsp<int64_t>(a, a.L.act_phase) + p) == 0) return;  // uniform: nothing active in this round
-  const int64_t nblk = p == 0 ? *wsp<int64_t>(a, a.L.nblk) : work_cnt[p % 2];
+  const int64_t nblk = p == 0 ? *wsp<int64_t>(a, a.L.nblk) : wsp<int64_t>(a, a.L.work_cnt)[p];
   if ((int64_t)blockIdx.x >= nblk) return;
   const int32_t* list = wsp<int32_t>(a, a.L.work) + (int64_t)(p % 2) * a.L.nblk_max;
   float* par = reinterpret_cast<float*>(lds + T::PAR);
@@ -1946,17 +1991,79 @@ __global__ __launch_bounds__(NTH) void gn_solve_kernel(StepArgs a, int p, int is
   const int ph = s_ph;
   const bool active = p == 0 ? ph == PH_INIT : evaluates_trials(ph);
   if (!active) return;
-  if (!solve_instance<R, true>(a, lds, inst, p, is_last != 0)) return;
-  // list this instance's batches for the next round (any order: each batch
-  // keeps its own partials slot and the solve sums them in batch order)
-  __shared__ int64_t s_base;
-  const int32_t b0 = first_blk[inst], b1 = first_blk[inst + 1];
-  if (threadIdx.x == 0)
-    s_base = (int64_t)atomicAdd(reinterpret_cast<unsigned long long*>(wsp<int64_t>(a, a.L.work_cnt) + (p + 1) % 2),
-                                (unsigned long long)(b1 - b0));
+  solve_instance<R, true, 0, true>(a, lds, inst, p, is_last != 0);
+}
+
+// The rounds from p0 on in one launch.  A step may need up to 1 + max_iter
+// (ls_max + 2) rounds, 62 by default, and most find every instance done, but
+// a pair of empty launches takes some 6 us all the same (FP32 step of 64
+// untrained instances at 1,100 samples on average: 13 rounds with work, 62
+// launched).  Here the workgroup that completes an instance's last batch of a
+// round solves the instance at once, and the grid (no more workgroups than
+// the device holds at once) waits for the solves, as in the persistent
+// kernel, and goes on until nothing is active.  Only for the last rounds: the
+// arrival costs every batch about 2 us, which few batches on an idle device
+// do not notice (all rounds this way: 5.3 -> 7.0 ms for 256 instances in
+// BF16).  Same evaluations and solves as the rounds of their own.
+template <class S, int NW, int PREC, int PF, int NTH>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1))) void gn_tail_kernel(StepArgs a, int p0,
+                                                                                             int max_rounds) {
+  using T = StepTraits<S, NW, PREC, PF, PK_HEAT, true>;
+  extern __shared__ __align__(16) char lds[];
+  __shared__ int s_ph, s_lt, s_last, s_abort;
+  __shared__ int64_t s_act, s_n;
+  __shared__ double qdl[TV * RMAX];
+  const int64_t* act_phase = wsp<int64_t>(a, a.L.act_phase);
+  if (ld_c(act_phase + p0) == 0) return;  // uniform over the grid: nothing active
+  float* par = reinterpret_cast<float*>(lds + T::PAR);
+  T::E0::PC::load(par, a.params, a.pi, a.depth, NW * 64);
   __syncthreads();
-  int32_t* list = wsp<int32_t>(a, a.L.work) + (int64_t)((p + 1) % 2) * a.L.nblk_max;
-  for (int32_t i = threadIdx.x; i < b1 - b0; i += blockDim.x) list[s_base + i] = b0 + i;
+  const int32_t* blk_inst = wsp<int32_t>(a, a.L.blk_inst);
+  const int32_t* first_blk = wsp<int32_t>(a, a.L.first_blk);
+  const GNState* state = wsp<GNState>(a, a.L.state);
+  uint64_t target = 0;  // solves of the rounds before, once they are all counted
+  for (int p = 0; p < p0; ++p) target += (uint64_t)ld_c(act_phase + p);
+  for (int p = p0; p <= max_rounds; ++p) {
+    if (threadIdx.x == 0) {  // final: written by round p - 1's solves
+      s_act = ld_c(act_phase + p);
+      s_n = ld_c(wsp<int64_t>(a, a.L.work_cnt) + p);
+    }
+    __syncthreads();
+    const int64_t act = s_act, n = s_n;
+    __syncthreads();
+    if (act == 0) break;
+    target += (uint64_t)act;
+    const int32_t* list = wsp<int32_t>(a, a.L.work) + (int64_t)(p % 2) * a.L.nblk_max;
+    for (int64_t it = blockIdx.x; it < n; it += gridDim.x) {
+      const int64_t blk = (int64_t)ld_c(list + it);
+      const int inst = blk_inst[blk];
+      if (threadIdx.x == 0) {
+        s_ph = ld_c(&state[inst].phase);
+        s_lt = ld_c(&state[inst].ls_tried);
+      }
+      __syncthreads();
+      const int ph = s_ph, lt = s_lt;
+      __syncthreads();
+      if (ph == PH_TRIALS && lt > 0)
+        eval_trials_batch<S, NW, PREC, PF, false>(a, lds, par, qdl, blk, inst, -1, false);
+      else
+        eval_trials_batch<S, NW, PREC, PF, true, true>(a, lds, par, qdl, blk, inst, -1, false);
+      // arrival: the partials of this batch are complete in memory
+      wait_mem();
+      __syncthreads();
+      if (threadIdx.x == 0)
+        s_last = atomicAdd(wsp<uint32_t>(a, a.L.inst_cnt) + inst, 1u) + 1 ==
+                 (uint32_t)(first_blk[inst + 1] - first_blk[inst]);
+      __syncthreads();
+      const bool last = s_last != 0;
+      __syncthreads();  // every thread has read s_last before thread 0 may write it again
+      if (last) solve_instance<S::R, true, NTH, true>(a, lds, inst, p, p == max_rounds);
+    }
+    if (threadIdx.x == 0) s_abort = wait_solved(wsp<uint64_t>(a, a.L.sync), target);
+    __syncthreads();
+    if (s_abort != 0) break;
+  }
+  leave_rounds(a);
 }
 
 // NWS: the waves of the persistent kernel whose solve the rounds repeat (its
@@ -1985,10 +2092,30 @@ static crom_status launch_gn_rounds_t(StepArgs a, int max_rounds, hipStream_t st
   if ((s = resident_grid(rc, reinterpret_cast<const void*>(kr), NW * 64, lds_bytes, &g)) != CROM_OK) return s;
   if (g > a.L.nblk_max) g = a.L.nblk_max;
   if (g < 1) g = 1;
+  // launches of their own: two rounds per iteration (a trial, now and then a
+  // shorter one), more of them the larger the batch, whose late rounds still
+  // fill the device; then the tail.  FP32 step of 64 untrained instances
+  // (4.5 k batches) 1.62 -> 1.42 ms, BF16 1.73 -> 1.63; 256 instances (18 k)
+  // with the tail after two rounds per iteration 5.30 -> 5.46 (BF16)
+  const int64_t share = std::max<int64_t>(1, a.L.nblk_max / 4096);
+  const int own = REV ? (int)std::min<int64_t>(max_rounds, 2 * share * a.max_iter) : max_rounds;
   timer_mark(st);
-  for (int p = 0; p <= max_rounds; ++p) {
+  for (int p = 0; p <= own; ++p) {
     hipLaunchKernelGGL(kr, dim3((unsigned)g), dim3(NW * 64), lds_bytes, st, a, p);
     hipLaunchKernelGGL(ks, dim3((unsigned)a.n_inst), dim3(NWS * 64), SOLVE_LDS, st, a, p, (int)(p == max_rounds));
+  }
+  if constexpr (REV) {
+    if (max_rounds > own) {
+      static_assert(NRED <= NW * 64, "one thread per reduced entry");
+      static_assert(SOLVE_LDS <= T::PAR, "solve scratch fits below the parameter cache");
+      auto kt = gn_tail_kernel<S, NW, PREC, PF, NWS * 64>;
+      if ((s = set_lds(kt, lds_bytes)) != CROM_OK) return s;
+      static ResidentCache rct;
+      int64_t gt = 0;
+      if ((s = resident_grid(rct, reinterpret_cast<const void*>(kt), NW * 64, lds_bytes, &gt)) != CROM_OK) return s;
+      gt = std::max<int64_t>(1, std::min(gt, a.L.nblk_max));
+      hipLaunchKernelGGL(kt, dim3((unsigned)gt), dim3(NW * 64), lds_bytes, st, a, own + 1, max_rounds);
+    }
   }
   timer_mark(st);
   return hip_check(hipGetLastError(), "round launches");
@@ -2134,7 +2261,7 @@ static crom_status step_prec(int prec, const StepArgs& a, int rounds, hipStream_
     // best for full batches (three workgroups per CU with the reverse pass)
     constexpr int NWL = S::MTILES < CROM_LIN_NW ? S::MTILES : CROM_LIN_NW;
     constexpr int WPE_REV = S::R > 8 ? 2 : CROM_LIN_REV_WPE;  // r = 16: the Jacobian sums need the registers
-    if (prec == CROM_PREC_FP32) return launch_lls<S, NWF, PREC_FP32, 0, 1>(a, st);
+    if (prec == CROM_PREC_FP32) return launch_lls<S, NWF, PREC_FP32, CROM_F32_PF, 1, (S::R > 8 ? 2 : CROM_F32_LIN_WPE)>(a, st);
     if (prec == CROM_PREC_BF16) return launch_lls<S, NWL, PREC_BF16, CROM_LIN_PF, CROM_LIN_WPE, WPE_REV>(a, st);
     if constexpr (ALL) {
       if (prec == CROM_PREC_BF16_PURE)
@@ -2147,7 +2274,8 @@ static crom_status step_prec(int prec, const StepArgs& a, int rounds, hipStream_
     // the evaluations in the linearised step's configuration (the fastest
     // for full batches), the solves with the persistent kernel's threads
     constexpr int NWL = S::MTILES < CROM_LIN_NW ? S::MTILES : CROM_LIN_NW;
-    if (prec == CROM_PREC_FP32) return launch_gn_rounds<S, NWF, PREC_FP32, 0, 1, 1, NWF>(a, rounds, st);
+    if (prec == CROM_PREC_FP32)
+      return launch_gn_rounds<S, NWF, PREC_FP32, CROM_F32_PF, 1, CROM_F32_GN_WPE, NWF>(a, rounds, st);
     if (prec == CROM_PREC_BF16)
       return launch_gn_rounds<S, NWL, PREC_BF16, CROM_LIN_PF, CROM_LIN_WPE, CROM_GN_REV_WPE, NWB>(a, rounds, st);
     if constexpr (ALL) {
