@@ -307,7 +307,7 @@ template <class S, int NW, int PREC, int QC, int HC>
 static crom_status decode_shape(const DecodeArgs& a0, bool xt, int d2, bool qt, hipStream_t st) {
   DecodeArgs a = a0;
   const bool spatial = xt || d2 != D2_NONE;
-  if constexpr (PREC == PREC_FP32) {
+  if constexpr (PREC == PREC_FP32 && S::R >= 8) {  // with 3 latents the forward tangents are as few
     if (qt) {
       bool done = false;
       crom_status s = CROM_OK;

@@ -455,18 +455,21 @@ constexpr int MSE_BLOCKS = 1024;
 // 4,999 points took 382 us layer by layer and takes 182, the gradients of
 // 16 snapshots of 16,384 points 0.92 ms and 0.33.
 static bool fused_shape(const crom_net* n) {
-  return n->width == TF_W && n->m == 2 && n->d == 1 && n->act == CROM_ACT_ELU && n->depth >= 3 && n->depth <= 5 &&
-         n->precision != CROM_PREC_FP32;
+  return n->width == TF_W && n->m == 2 && n->d == 1 && n->act == CROM_ACT_ELU && n->depth >= 3 && n->depth <= 5;
 }
 
 // Rows of a snapshot that one workgroup of the fused pass sums at a time.
 // Training: colsum's chunks (whose FP32 sums the encoder's gradient repeats
-// bit for bit).  A vector-Jacobian product has no such follower: while there
+// bit for bit in bfloat16; in FP32 nothing hangs on it, and single blocks
+// share out evenly).  A vector-Jacobian product has no such follower: while there
 // are compute units for it, one block of rows per workgroup (120 instead of
 // 60 workgroups for 3 latents at 4,999 points: 54 -> 35 us, and 7 -> 14 us to
 // add their gradients).
+template <class T>
 static int64_t fused_chunk_rows(int64_t P, int B, bool vjp) {
-  if (vjp && (P + TF_ROWS - 1) / TF_ROWS * B <= TF_MAX_WG) return TF_ROWS;
+  constexpr int ROWS = FusedTile<T>::ROWS;
+  const int64_t blocks = (P + ROWS - 1) / ROWS * B;
+  if (sizeof(T) == 2 ? vjp && blocks <= TF_MAX_WG : blocks <= 8 * TF_MAX_WG) return ROWS;
   return (P + row_chunks(P, B) - 1) / row_chunks(P, B);
 }
 
@@ -480,9 +483,9 @@ struct DecoderPass {
   T* gt[16];  // sine networks: cos(z_l) of each hidden layer
   float *c, *g, *dg, *part;
   double *cpart, *csum, *mpart;
-  bf16x8* frags;  // the fused pass: packed weights, sums carried between blocks
+  void* frags;  // the fused pass: packed weights, sums carried between blocks, first activations
   f32x4* carry;
-  __bf16* a0;
+  T* a0;
   static size_t bytes(const crom_net* n, int B, int64_t P) {
     Carve cv{nullptr, 0};
     DecoderPass d;
@@ -493,13 +496,13 @@ struct DecoderPass {
     const int64_t rows = (int64_t)B * P;
     const int W = n->width, depth = n->depth, D = n->d;
     if (fused_shape(n)) {
-      const int64_t rows = std::min(fused_chunk_rows(P, B, true), fused_chunk_rows(P, B, false));
+      const int64_t rows = std::min(fused_chunk_rows<T>(P, B, true), fused_chunk_rows<T>(P, B, false));
       const int64_t items = (P + rows - 1) / rows * B, wgs = items < TF_MAX_WG ? items : TF_MAX_WG;
-      frags = cv.take<bf16x8>((size_t)(depth - 1) * 2 * TF_FRAGS);
+      frags = cv.take<f32x4>((size_t)(depth - 1) * 2 * FusedTile<T>::FRAGS);
       c = cv.take<float>((size_t)B * W);
       part = cv.take<float>((size_t)wgs * (depth - 1) * TF_MAT);
       carry = cv.take<f32x4>((size_t)wgs * 3 * TF_THREADS);
-      a0 = cv.take<__bf16>((size_t)wgs * TF_ROWS * TF_LD);
+      a0 = cv.take<T>((size_t)wgs * FusedTile<T>::ROWS * FusedTile<T>::LD);
       cpart = cv.take<double>((size_t)items * 3 * W);
       mpart = cv.take<double>((size_t)wgs * (2 * W + 2));
       csum = cv.take<double>((size_t)B * 3 * W);
@@ -522,14 +525,14 @@ struct DecoderPass {
   }
 };
 
-template <int L>
+template <class T, int L>
 static crom_status fused_fwd_bwd(const crom_net* n, const float* x, int B, int64_t P, const float* q, const float* u,
-                                 const float* dg_in, float* grad, float* dq, float* loss, DecoderPass<__bf16>& ws,
-                                 hipStream_t st) {
+                                 const float* dg_in, float* grad, float* dq, float* loss, DecoderPass<T>& ws, hipStream_t st) {
+  using F = FusedTile<T>;
   const int r = n->r;
   const ParamIndex pi = param_index(2, r, 1, TF_W, L + 1);
-  hipLaunchKernelGGL(fused_prep_kernel, dim3((L * 2 * TF_FRAGS + 255) / 256), dim3(256), 0, st, n->params, pi, L, q, B,
-                     r, ws.frags, ws.c);
+  hipLaunchKernelGGL(fused_prep_kernel<T>, dim3((L * 2 * F::FRAGS + 255) / 256), dim3(256), 0, st, n->params, pi, L, q,
+                     B, r, static_cast<typename F::frag*>(ws.frags), ws.c);
   FusedArgs a{};
   a.params = n->params;
   a.pi = pi;
@@ -540,7 +543,7 @@ static crom_status fused_fwd_bwd(const crom_net* n, const float* x, int B, int64
   a.dg_in = dg_in;
   a.P = P;
   a.r = r;
-  a.chunk_rows = fused_chunk_rows(P, B, dg_in != nullptr);
+  a.chunk_rows = fused_chunk_rows<T>(P, B, dg_in != nullptr);
   a.chunks = (int)((P + a.chunk_rows - 1) / a.chunk_rows);  // rounding up may leave the last ones without rows
   a.items = (int64_t)B * a.chunks;
   a.n = (float)((int64_t)B * P);
@@ -550,10 +553,10 @@ static crom_status fused_fwd_bwd(const crom_net* n, const float* x, int B, int64
   a.spart = ws.cpart;
   a.opart = ws.mpart;
   const int wgs = (int)(a.items < TF_MAX_WG ? a.items : TF_MAX_WG);
-  auto k = fused_train_kernel<L>;
-  crom_status s = set_lds(k, (int)sizeof(FusedLds<L>));
+  auto k = fused_train_kernel<T, L>;
+  crom_status s = set_lds(k, (int)sizeof(FusedLds<T, L>));
   if (s != CROM_OK) return s;
-  hipLaunchKernelGGL(k, dim3(wgs), dim3(TF_THREADS), sizeof(FusedLds<L>), st, a);
+  hipLaunchKernelGGL(k, dim3(wgs), dim3(TF_THREADS), sizeof(FusedLds<T, L>), st, a);
   FusedReduceArgs f{ws.part, ws.mpart, ws.cpart, wgs, L, a.chunks, pi, grad, dg_in ? nullptr : loss,
                     (double)((int64_t)B * P), ws.csum, B};
   hipLaunchKernelGGL(fused_reduce_kernel, dim3(L * TF_MAT / 64 + (TF_W + 2 + 63) / 64 + B * (3 * TF_W / 64)), dim3(256),
@@ -573,12 +576,10 @@ static crom_status decoder_fwd_bwd(const crom_net* n, const float* x, int B, int
   const float* prm = n->params;
   const bool sine = n->act == CROM_ACT_SINE;  // bfloat16 row kernels only (checked at entry)
   crom_status s = CROM_OK;
-  if constexpr (sizeof(T) == 2) {
-    if (fused_shape(n)) {
-      if (depth == 3) return fused_fwd_bwd<2>(n, x, B, P, q, u, dg_in, grad, dq, loss, ws, st);
-      if (depth == 4) return fused_fwd_bwd<3>(n, x, B, P, q, u, dg_in, grad, dq, loss, ws, st);
-      return fused_fwd_bwd<4>(n, x, B, P, q, u, dg_in, grad, dq, loss, ws, st);
-    }
+  if (fused_shape(n)) {
+    if (depth == 3) return fused_fwd_bwd<T, 2>(n, x, B, P, q, u, dg_in, grad, dq, loss, ws, st);
+    if (depth == 4) return fused_fwd_bwd<T, 3>(n, x, B, P, q, u, dg_in, grad, dq, loss, ws, st);
+    return fused_fwd_bwd<T, 4>(n, x, B, P, q, u, dg_in, grad, dq, loss, ws, st);
   }
   // weights in the GEMM precision
   for (int l = 1; l < depth; ++l)
