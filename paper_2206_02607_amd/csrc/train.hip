@@ -559,8 +559,8 @@ static crom_status fused_fwd_bwd(const crom_net* n, const float* x, int B, int64
   hipLaunchKernelGGL(k, dim3(wgs), dim3(TF_THREADS), sizeof(FusedLds<T, L>), st, a);
   FusedReduceArgs f{ws.part, ws.mpart, ws.cpart, wgs, L, a.chunks, pi, grad, dg_in ? nullptr : loss,
                     (double)((int64_t)B * P), ws.csum, B};
-  hipLaunchKernelGGL(fused_reduce_kernel, dim3(L * TF_MAT / 64 + (TF_W + 2 + 63) / 64 + B * (3 * TF_W / 64)), dim3(256),
-                     0, st, f);
+  hipLaunchKernelGGL(fused_reduce_kernel, dim3(L * TF_MAT / 64 + (TF_W + 2 + 63) / 64 + B * (3 * TF_W / 64)),
+                     dim3(TF_LANES * 64), 0, st, f);
   hipLaunchKernelGGL(layer1_grad_kernel, dim3((TF_W * (2 + r) + TF_W + B * r + 3) / 4), dim3(256), 0, st, ws.csum, q,
                      n->params + pi.w[0], B, TF_W, 2, r, grad + pi.w[0], grad + pi.b[0], dq);
   return hip_check(hipGetLastError(), "fused training pass");
@@ -715,22 +715,15 @@ static crom_status decoder_fwd_bwd(const crom_net* n, const float* x, int B, int
 // Encoder: E1 [hidden][n_in], c1 [hidden], E2 [r][hidden], c2 [r] (FP32).
 template <class T>
 struct EncoderPass {
-  T *e1, *ub, *h, *dh;
+  T *ub, *dh;  // the snapshots (bfloat16 only) and the hidden layer's gradient as operands of dE1
   float *q, *dq, *h32, *kpart;
-  double *cpart, *csum;
   void carve(Carve& cv, const crom_encoder* e, int B) {
-    e1 = cv.take<T>((size_t)e->hidden * e->n_in);
-    ub = cv.take<T>((size_t)B * e->n_in);
-    h = cv.take<T>((size_t)B * e->hidden);
+    ub = sizeof(T) == 2 ? cv.take<T>((size_t)B * e->n_in) : nullptr;
     dh = cv.take<T>((size_t)B * e->hidden);
     q = cv.take<float>((size_t)B * e->r);
     dq = cv.take<float>((size_t)B * e->r);
     h32 = cv.take<float>((size_t)B * e->hidden);
     kpart = cv.take<float>((size_t)MAX_SPLITS * B * e->hidden);
-    // column sums over the batch of dz1 [B][hidden] and of dq [B][r]
-    const int cols = e->hidden > e->r ? e->hidden : e->r;
-    cpart = cv.take<double>((size_t)COLSUM_CHUNKS * cols);
-    csum = cv.take<double>((size_t)cols);
   }
 };
 
@@ -743,70 +736,194 @@ static ParamIndex enc_index(const crom_encoder* e) {
   return pi;
 }
 
+// First layer of the dense encoder, split over K: part[z][b][n] = the products
+// of u [B][K] and E1 [N][K] over K-range z (a multiple of the K tile), FP32.
+// One wave per 16 snapshots x 16 units and range; the operands are read as
+// FP32 and rounded here (converting E1 and u first, in launches of their own,
+// read and wrote 29 MB more: 23 us for 16,384 -> 256 against 8).  Bfloat16:
+// ub (NULL: none) also receives u in bfloat16.  Same operands, K order and
+// ranges as gemm_kernel with split K.
 template <class T>
-static crom_status encoder_fwd(const crom_encoder* e, const float* u, int B, EncoderPass<T>& ws, hipStream_t st) {
-  const ParamIndex pi = enc_index(e);
-  const float* prm = e->params;
-  hipLaunchKernelGGL((convert_kernel<T>), dim3(grid_for((int64_t)e->hidden * e->n_in)), dim3(256), 0, st, prm,
-                     ws.e1, (int64_t)e->hidden * e->n_in);
-  hipLaunchKernelGGL((convert_kernel<T>), dim3(grid_for((int64_t)B * e->n_in)), dim3(256), 0, st, u, ws.ub,
-                     (int64_t)B * e->n_in);
-  // h = ELU(u E1^T + c1)  [B][hidden], kept in T (for the GEMM) and FP32
-  GemmArgs g = gemm_args(B, e->hidden, e->n_in, ws.ub, e->n_in, ws.e1, e->n_in);
-  g.bias = prm + pi.b[0];
-  g.C = ws.h32;
-  g.ldc = e->hidden;
-  g.part = ws.kpart;  // few rows, long K: split K over blocks
-  crom_status s = gemm<T, false, true, EPI_BIAS_ELU>(g, st);
-  if (s != CROM_OK) return s;
-  hipLaunchKernelGGL((convert_kernel<T>), dim3(grid_for((int64_t)B * e->hidden)), dim3(256), 0, st, ws.h32, ws.h,
-                     (int64_t)B * e->hidden);
-  // q = h E2^T + c2 (FP32 product of the FP32 activations)
-  GemmArgs g2 = gemm_args(B, e->r, e->hidden, ws.h32, e->hidden, prm + pi.w[1], e->hidden);
-  g2.bias = prm + pi.b[1];
-  g2.C = ws.q;
-  g2.ldc = e->r;
-  return gemm<float, false, true, EPI_BIAS>(g2, st);
+__global__ __launch_bounds__(256) void enc_part_kernel(const float* __restrict__ u, const float* __restrict__ E1, int B,
+                                                       int N, int64_t K, int64_t kchunk, int vec, T* __restrict__ ub,
+                                                       float* __restrict__ part) {
+  constexpr bool BF = sizeof(T) == 2;
+  constexpr int STEP = BF ? 32 : 4, E = STEP / 4;  // K of one product; K per lane
+  typedef T frag __attribute__((ext_vector_type(E)));
+  const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
+  const int n0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * 16, b0 = blockIdx.z * 16;
+  if (n0 >= N) return;
+  const int64_t k0 = blockIdx.x * kchunk, k1 = k0 + kchunk < K ? k0 + kchunk : K;
+  auto load = [&](const float* row, bool ok, int64_t k) {
+    frag f;
+    if constexpr (BF) {
+      if (vec && ok && k + 8 <= k1) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(row + k), y = *reinterpret_cast<const f32x4*>(row + k + 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          f[e] = (T)x[e];
+          f[4 + e] = (T)y[e];
+        }
+        return f;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) f[e] = ok && k + e < k1 ? (T)row[k + e] : (T)0.0f;
+    return f;
+  };
+  const int b = b0 + lr, n = n0 + lr;
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+  for (int64_t ks = k0; ks < k1; ks += STEP) {
+    const int64_t k = ks + E * lg;
+    const frag x = load(u + (int64_t)b * K, b < B, k), y = load(E1 + (int64_t)n * K, n < N, k);
+    if constexpr (BF) {
+      if (ub && n0 == 0 && b < B) {
+        if (vec && K % 8 == 0 && k + 8 <= k1) {
+          *reinterpret_cast<frag*>(&ub[(int64_t)b * K + k]) = x;
+        } else {
+#pragma unroll
+          for (int e = 0; e < E; ++e)
+            if (k + e < k1) ub[(int64_t)b * K + k + e] = x[e];
+        }
+      }
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, acc, 0, 0, 0);
+    } else {
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0], y[0], acc, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int row = b0 + 4 * lg + v;
+    if (row < B && n < N) part[((int64_t)blockIdx.x * B + row) * N + n] = acc[v];
+  }
+}
+
+// q [B][r] = h [B][K] E2^T + c2, FP32 products in K order, one wave per 16 x 16
+// outputs; q2 (NULL: none): a second copy.
+__global__ __launch_bounds__(64) void enc_latent_kernel(const float* __restrict__ h, const float* __restrict__ E2,
+                                                        const float* __restrict__ c2, int B, int r, int K,
+                                                        float* __restrict__ q, float* __restrict__ q2) {
+  const int lr = threadIdx.x & 15, lg = threadIdx.x >> 4;
+  const int b = blockIdx.y * 16 + lr, n = blockIdx.x * 16 + lr;
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  constexpr int U = 16;  // products whose operands are in flight together
+  for (int k0 = 0; k0 < K; k0 += 4 * U) {
+    float x[U], y[U];
+#pragma unroll
+    for (int s = 0; s < U; ++s) {
+      const int k = k0 + 4 * s + lg;
+      x[s] = b < B && k < K ? h[(int64_t)b * K + k] : 0.0f;
+      y[s] = n < r && k < K ? E2[(int64_t)n * K + k] : 0.0f;
+    }
+#pragma unroll
+    for (int s = 0; s < U; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[s], y[s], acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int row = blockIdx.y * 16 + 4 * lg + v;
+    if (row < B && n < r) {
+      const float t = acc[v] + c2[n];
+      q[row * r + n] = t;
+      if (q2) q2[row * r + n] = t;
+    }
+  }
 }
 
 template <class T>
-static crom_status encoder_bwd(const crom_encoder* e, int B, const float* dq, float* grad, EncoderPass<T>& ws,
-                               float* split_part, hipStream_t st) {
+static crom_status encoder_fwd(const crom_encoder* e, const float* u, int B, EncoderPass<T>& ws, float* q_out,
+                               hipStream_t st) {
   const ParamIndex pi = enc_index(e);
   const float* prm = e->params;
-  crom_status s;
-  // dE2 = dq^T h  [r][hidden], dc2 = sum_b dq
-  {
-    GemmArgs g = gemm_args(e->r, e->hidden, B, dq, e->r, ws.h32, e->hidden);
-    g.C = grad + pi.w[1];
-    g.ldc = e->hidden;
-    if ((s = gemm<float, true, false, EPI_NONE>(g, st)) != CROM_OK) return s;
-    colsum<float>(dq, e->r, e->r, 1, B, nullptr, 1, 0, 1, ws.cpart, ws.csum, st);
-    hipLaunchKernelGGL(d2f_kernel, dim3(1), dim3(64), 0, st, ws.csum, grad + pi.b[1], (int64_t)e->r);
+  // h = ELU(u E1^T + c1)  [B][hidden]: few rows, long K, so K is split
+  constexpr int BK = sizeof(T) == 2 ? 64 : 32;
+  const int64_t tiles = (int64_t)((e->hidden + 63) / 64) * ((B + 63) / 64);
+  int64_t splits = std::min<int64_t>({(1024 + tiles - 1) / tiles, ((int64_t)e->n_in + BK - 1) / BK, MAX_SPLITS});
+  if (splits < 1) splits = 1;
+  const int64_t kc = (((int64_t)e->n_in + splits - 1) / splits + BK - 1) / BK * BK;
+  splits = (e->n_in + kc - 1) / kc;
+  const int vec = e->n_in % 4 == 0 && (reinterpret_cast<uintptr_t>(u) | reinterpret_cast<uintptr_t>(prm)) % 16 == 0;
+  if ((B + 15) / 16 > 65535) return fail(CROM_ERR_UNSUPPORTED, "too many snapshots");
+  hipLaunchKernelGGL(enc_part_kernel<T>, dim3((unsigned)splits, (e->hidden + 63) / 64, (B + 15) / 16), dim3(256), 0, st,
+                     u, prm, B, e->hidden, (int64_t)e->n_in, kc, vec, ws.ub, ws.kpart);
+  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)(((int64_t)B * e->hidden + 63) / 64)), dim3(256), 0, st,
+                     ws.kpart, (int)splits, B, e->hidden, ws.h32, (int64_t)e->hidden, 0, (int)EPI_BIAS_ELU,
+                     prm + pi.b[0]);
+  // q = h E2^T + c2 (FP32 product of the FP32 activations)
+  hipLaunchKernelGGL(enc_latent_kernel, dim3((e->r + 15) / 16, (B + 15) / 16), dim3(64), 0, st, ws.h32, prm + pi.w[1],
+                     prm + pi.b[1], B, e->r, e->hidden, ws.q, q_out);
+  return hip_check(hipGetLastError(), "encoder forward");
+}
+
+// Backward of the dense encoder's small layers, one wave per 16 hidden units
+// (nine launches of the general products and sums took 60 us for 16 snapshots
+// and 256 units):
+//   dz1 [B][hidden] = (dq E2) * ELU'(h), in T (FP32 products in K order),
+//   dc1 = sum_b dz1,  dE2 [r][hidden] = dq^T h,  dc2 = sum_b dq  (FP64 sums).
+template <class T>
+__global__ __launch_bounds__(64) void enc_bwd_kernel(const float* __restrict__ dq, const float* __restrict__ E2,
+                                                     const float* __restrict__ h, int B, int r, int N,
+                                                     T* __restrict__ dz1, float* __restrict__ dc1,
+                                                     float* __restrict__ dE2, float* __restrict__ dc2) {
+  constexpr int RM = 16;  // largest latent size
+  const int lr = threadIdx.x & 15, lg = threadIdx.x >> 4;
+  const int n = blockIdx.x * 16 + lr;
+  double s1 = 0.0, s2[RM];
+#pragma unroll
+  for (int k = 0; k < RM; ++k) s2[k] = 0.0;
+  for (int b0 = 0; b0 < B; b0 += 16) {
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k0 = 0; k0 < RM; k0 += 4) {
+      const int k = k0 + lg;
+      const float x = b0 + lr < B && k < r ? dq[(b0 + lr) * r + k] : 0.0f;
+      const float y = n < N && k < r ? E2[(int64_t)k * N + n] : 0.0f;
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int b = b0 + 4 * lg + v;
+      if (b >= B || n >= N) continue;
+      const float hv = h[(int64_t)b * N + n], z = acc[v] * elu_d1_from_a(hv);
+      dz1[(int64_t)b * N + n] = (T)z;
+      s1 += (double)z;
+#pragma unroll
+      for (int k = 0; k < RM; ++k)
+        if (k < r) s2[k] += (double)dq[b * r + k] * (double)hv;
+    }
   }
-  // dz1 = (dq E2) * ELU'(h)  [B][hidden]
-  {
-    GemmArgs g = gemm_args(B, e->hidden, e->r, dq, e->r, prm + pi.w[1], e->hidden);
-    g.gate = ws.h32;
-    g.ldg = e->hidden;
-    g.C = ws.h32;  // h is consumed by the gate in the same element: safe in place
-    g.ldc = e->hidden;
-    if ((s = gemm<float, false, false, EPI_DELU>(g, st)) != CROM_OK) return s;
+  auto groups = [](double s) {
+    s += __shfl_xor(s, 16);
+    return s + __shfl_xor(s, 32);
+  };
+  s1 = groups(s1);
+#pragma unroll
+  for (int k = 0; k < RM; ++k) s2[k] = groups(s2[k]);
+  if (lg == 0 && n < N) {
+    dc1[n] = (float)s1;
+#pragma unroll
+    for (int k = 0; k < RM; ++k)
+      if (k < r) dE2[(int64_t)k * N + n] = (float)s2[k];
   }
-  hipLaunchKernelGGL((convert_kernel<T>), dim3(grid_for((int64_t)B * e->hidden)), dim3(256), 0, st, ws.h32, ws.dh,
-                     (int64_t)B * e->hidden);
-  // dE1 = dz1^T u  [hidden][n_in];  dc1 = sum_b dz1
-  {
-    GemmArgs g = gemm_args(e->hidden, e->n_in, B, ws.dh, e->hidden, ws.ub, e->n_in);
-    g.C = grad + pi.w[0];
-    g.ldc = e->n_in;
-    if ((s = gemm<T, true, false, EPI_NONE>(g, st)) != CROM_OK) return s;
-    colsum<float>(ws.h32, e->hidden, e->hidden, 1, B, nullptr, 1, 0, 1, ws.cpart, ws.csum, st);
-    hipLaunchKernelGGL(d2f_kernel, dim3(grid_for(e->hidden)), dim3(256), 0, st, ws.csum, grad + pi.b[0],
-                       (int64_t)e->hidden);
+  if (blockIdx.x == 0 && threadIdx.x < r) {
+    double s = 0.0;
+    for (int b = 0; b < B; ++b) s += (double)dq[b * r + threadIdx.x];
+    dc2[threadIdx.x] = (float)s;
   }
-  (void)split_part;
-  return hip_check(hipGetLastError(), "encoder backward");
+}
+
+template <class T>
+static crom_status encoder_bwd(const crom_encoder* e, const float* u, int B, const float* dq, float* grad,
+                               EncoderPass<T>& ws, hipStream_t st) {
+  const ParamIndex pi = enc_index(e);
+  hipLaunchKernelGGL(enc_bwd_kernel<T>, dim3((e->hidden + 15) / 16), dim3(64), 0, st, dq, e->params + pi.w[1], ws.h32, B,
+                     e->r, e->hidden, ws.dh, grad + pi.b[0], grad + pi.w[1], grad + pi.b[1]);
+  // dE1 = dz1^T u  [hidden][n_in]
+  const void* ut = ws.ub ? static_cast<const void*>(ws.ub) : u;
+  GemmArgs g = gemm_args(e->hidden, e->n_in, B, ws.dh, e->hidden, ut, e->n_in);
+  g.C = grad + pi.w[0];
+  g.ldc = e->n_in;
+  return gemm<T, true, false, EPI_NONE>(g, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -884,65 +1001,93 @@ __global__ __launch_bounds__(256) void conv_fwd_kernel(const float* __restrict__
   }
 }
 
-// out[b][o] = act(bias[o] + sum_i W[o][i] in[b][i])  (act: ELU or none)
-__global__ __launch_bounds__(256) void dense_fwd_kernel(const float* __restrict__ in, const float* __restrict__ W,
-                                                       const float* __restrict__ bias, int B, int64_t n_in,
-                                                       int n_out, int elu, float* __restrict__ out) {
-  const int64_t total = (int64_t)B * n_out;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int o = (int)(e % n_out);
-    const int64_t b = e / n_out;
-    float s = bias[o];
-    for (int64_t i = 0; i < n_in; ++i) s += W[o * n_in + i] * in[b * n_in + i];
-    out[e] = elu ? elu_f(s) : s;
+// The two dense layers on top, a workgroup per snapshot: h = ELU(E1 x + c1)
+// (n_mid values), q = E2 h + c2 (n_out), each output one thread's sum in input
+// order; q2 (NULL: none): a second copy of q.
+__global__ __launch_bounds__(256) void dense_fwd_kernel(const float* __restrict__ x, const float* __restrict__ E1,
+                                                       const float* __restrict__ c1, const float* __restrict__ E2,
+                                                       const float* __restrict__ c2, int64_t n_in, int n_mid, int n_out,
+                                                       float* __restrict__ h, float* __restrict__ q,
+                                                       float* __restrict__ q2) {
+  const int64_t b = blockIdx.x;
+  auto row = [](const float* W, float bias, const float* in, int64_t n) {
+    float s = bias;
+#pragma unroll 8
+    for (int64_t i = 0; i < n; ++i) s += W[i] * in[i];
+    return s;
+  };
+  for (int o = threadIdx.x; o < n_mid; o += blockDim.x)
+    h[b * n_mid + o] = elu_f(row(E1 + o * n_in, c1[o], x + b * n_in, n_in));
+  __syncthreads();
+  for (int o = threadIdx.x; o < n_out; o += blockDim.x) {
+    const float s = row(E2 + (int64_t)o * n_mid, c2[o], h + b * n_mid, n_mid);
+    q[b * n_out + o] = s;
+    if (q2) q2[b * n_out + o] = s;
   }
 }
 
-// dW[o][i] = sum_b dy[b][o] x[b][i], db[o] = sum_b dy[b][o] (FP64 sums over b in order)
-__global__ __launch_bounds__(256) void dense_wgrad_kernel(const float* __restrict__ dy, const float* __restrict__ x,
-                                                         int B, int64_t n_in, int n_out, float* __restrict__ dW,
-                                                         float* __restrict__ db) {
-  const int64_t total = (int64_t)n_out * n_in + n_out;
+// Backward of one dense layer, an output per thread:
+//   dW[o][i] = sum_b dy[b][o] x[b][i], db[o] = sum_b dy[b][o] (FP64 sums over b in order),
+//   dx[b][i] = (sum_o dy[b][o] W[o][i]) * ELU'(a[b][i])  (dx NULL: none)
+__global__ __launch_bounds__(256) void dense_bwd_kernel(const float* __restrict__ dy, const float* __restrict__ x,
+                                                       const float* __restrict__ W, const float* __restrict__ a, int B,
+                                                       int64_t n_in, int n_out, float* __restrict__ dW,
+                                                       float* __restrict__ db, float* __restrict__ dx) {
+  const int64_t nw = (int64_t)n_out * n_in, total = nw + n_out + (dx ? (int64_t)B * n_in : 0);
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    double s = 0.0;
-    if (e < (int64_t)n_out * n_in) {
+    if (e < nw) {
       const int64_t o = e / n_in, i = e % n_in;
+      double s = 0.0;
       for (int b = 0; b < B; ++b) s += (double)dy[(int64_t)b * n_out + o] * (double)x[(int64_t)b * n_in + i];
       dW[e] = (float)s;
-    } else {
-      const int64_t o = e - (int64_t)n_out * n_in;
+    } else if (e < nw + n_out) {
+      const int64_t o = e - nw;
+      double s = 0.0;
       for (int b = 0; b < B; ++b) s += (double)dy[(int64_t)b * n_out + o];
       db[o] = (float)s;
+    } else {
+      const int64_t j = e - nw - n_out, i = j % n_in, b = j / n_in;
+      float s = 0.0f;
+#pragma unroll 8
+      for (int o = 0; o < n_out; ++o) s += dy[b * n_out + o] * W[(int64_t)o * n_in + i];
+      dx[j] = s * delu_from_act(a[j]);
     }
   }
 }
 
-// dx[b][i] = (sum_o dy[b][o] W[o][i]) * ELU'(a[b][i])  (a NULL: no gate)
-__global__ __launch_bounds__(256) void dense_dx_kernel(const float* __restrict__ dy, const float* __restrict__ W,
-                                                      const float* __restrict__ a, int B, int64_t n_in, int n_out,
-                                                      float* __restrict__ dx) {
-  const int64_t total = (int64_t)B * n_in;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = e % n_in, b = e / n_in;
-    float s = 0.0f;
-    for (int o = 0; o < n_out; ++o) s += dy[b * n_out + o] * W[(int64_t)o * n_in + i];
-    dx[e] = a ? s * delu_from_act(a[e]) : s;
-  }
-}
-
-// Weight and bias gradients of one convolution, in two fixed-order stages.
-// Stage 1, block (e, chunk): e < d*d*6 takes W[o][c][k] =
-// sum_{b,j} dz[b][o][j] x(b, c, 4 j + k), e = d*d*6 + o the bias
-// sum_{b,j} dz[b][o][j], over the chunk's contiguous share of the (b, j)
-// pairs (each thread a fixed stride in FP64, then a tree in LDS) into
-// part[e][chunk].  Stage 2: each entry sums its chunks in order.
+// Backward of one convolution.  Blocks (e, chunk) of the first d*d*6 + d rows
+// of the grid: e < d*d*6 takes W[o][c][k] = sum_{b,j} dz[b][o][j] x(b, c, 4 j +
+// k), e = d*d*6 + o the bias sum_{b,j} dz[b][o][j], over the chunk's contiguous
+// share of the (b, j) pairs (each thread a fixed stride in FP64, then a tree in
+// LDS) into part[e][chunk]; conv_wgrad_final_kernel sums the chunks in order.
+// The other blocks: the input gradient, gated by the ELU of the layer below
+// (dzp NULL: none),
+//   dzp[b][c][i] = ELU'(a[b][c][i]) sum_o sum_{k: i = 4 j + k, 0 <= j < Lo} dz[b][o][j] W[o][c][k].
 constexpr int CONV_RED = 256, CONV_CHUNKS = 64;
-__global__ __launch_bounds__(CONV_RED) void conv_wgrad_kernel(const float* __restrict__ dz, const float* __restrict__ x,
-                                                             int64_t xb, int64_t xc, int64_t xi, int B, int d,
-                                                             int64_t Lo, double* __restrict__ part) {
+__global__ __launch_bounds__(CONV_RED) void conv_bwd_kernel(const float* __restrict__ dz, const float* __restrict__ x,
+                                                           int64_t xb, int64_t xc, int64_t xi,
+                                                           const float* __restrict__ W, const float* __restrict__ a,
+                                                           int B, int d, int64_t Li, int64_t Lo,
+                                                           double* __restrict__ part, float* __restrict__ dzp) {
   __shared__ double red[CONV_RED];
-  const int e = blockIdx.x, chunk = blockIdx.y;
+  const int e = blockIdx.x / CONV_CHUNKS, chunk = blockIdx.x % CONV_CHUNKS;
   const int nw = d * d * CONV_K;
+  if (e >= nw + d) {
+    const int64_t total = (int64_t)B * d * Li;
+    const int64_t first = blockIdx.x - (int64_t)(nw + d) * CONV_CHUNKS, blocks = gridDim.x - (int64_t)(nw + d) * CONV_CHUNKS;
+    for (int64_t p = first * blockDim.x + threadIdx.x; p < total; p += blocks * blockDim.x) {
+      const int64_t i = p % Li, bc = p / Li, b = bc / d;
+      const int c = (int)(bc % d);
+      float s = 0.0f;
+      for (int k = (int)(i % CONV_S); k < CONV_K; k += CONV_S) {
+        const int64_t j = (i - k) / CONV_S;
+        if (i < k || j >= Lo) continue;
+        for (int o = 0; o < d; ++o) s += dz[(b * d + o) * Lo + j] * W[((int64_t)o * d + c) * CONV_K + k];
+      }
+      dzp[p] = s * delu_from_act(a[p]);
+    }
+    return;
+  }
   const int64_t n = (int64_t)B * Lo;
   const int64_t per = (n + CONV_CHUNKS - 1) / CONV_CHUNKS;
   const int64_t t0 = chunk * per, t1 = t0 + per < n ? t0 + per : n;
@@ -969,43 +1114,26 @@ __global__ __launch_bounds__(CONV_RED) void conv_wgrad_kernel(const float* __res
   if (threadIdx.x == 0) part[(int64_t)e * CONV_CHUNKS + chunk] = red[0];
 }
 
-__global__ __launch_bounds__(64) void conv_wgrad_final_kernel(const double* __restrict__ part, int d,
-                                                             float* __restrict__ dW, float* __restrict__ db) {
-  const int nw = d * d * CONV_K;
-  for (int e = threadIdx.x; e < nw + d; e += blockDim.x) {
+// The weight and bias gradients of every convolution (a block each: W then b,
+// one after another in `grad`) from their partials.
+__global__ __launch_bounds__(64) void conv_wgrad_final_kernel(const double* __restrict__ part, int n,
+                                                             float* __restrict__ grad) {
+  part += (int64_t)blockIdx.x * n * CONV_CHUNKS;
+  grad += (int64_t)blockIdx.x * n;
+  for (int e = threadIdx.x; e < n; e += blockDim.x) {
     double s = 0.0;
+#pragma unroll 16
     for (int c = 0; c < CONV_CHUNKS; ++c) s += part[(int64_t)e * CONV_CHUNKS + c];
-    if (e < nw) dW[e] = (float)s;
-    else db[e - nw] = (float)s;
-  }
-}
-
-// Input gradient of one convolution, gated by the ELU of the layer below:
-// dzp[b][c][i] = ELU'(a[b][c][i]) sum_o sum_{k: i = 4 j + k, 0 <= j < Lo} dz[b][o][j] W[o][c][k]
-__global__ __launch_bounds__(256) void conv_dx_kernel(const float* __restrict__ dz, const float* __restrict__ W,
-                                                     const float* __restrict__ a, int B, int d, int64_t Li,
-                                                     int64_t Lo, float* __restrict__ dzp) {
-  const int64_t total = (int64_t)B * d * Li;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = e % Li, bc = e / Li;
-    const int c = (int)(bc % d);
-    const int64_t b = bc / d;
-    float s = 0.0f;
-    for (int k = (int)(i % CONV_S); k < CONV_K; k += CONV_S) {
-      const int64_t j = (i - k) / CONV_S;
-      if (i < k || j >= Lo) continue;
-      for (int o = 0; o < d; ++o) s += dz[(b * d + o) * Lo + j] * W[((int64_t)o * d + c) * CONV_K + k];
-    }
-    dzp[e] = s * delu_from_act(a[e]);
+    grad[e] = (float)s;
   }
 }
 
 struct ConvPass {
   float* a[CONV_MAXL + 1];  // a[l] = ELU(conv_l) [B][d][len[l]], l >= 1
   float *h, *q, *dq, *dh, *dz[2];
-  double* wpart;  // [d*d*6 + d][CONV_CHUNKS] weight-gradient partials
+  double* wpart;  // [convolutions][d*d*6 + d][CONV_CHUNKS] weight-gradient partials
   void carve(Carve& cv, const ConvShape& c, int B) {
-    wpart = cv.take<double>((size_t)(c.d * c.d * CONV_K + c.d) * CONV_CHUNKS);
+    wpart = cv.take<double>((size_t)c.nl * (c.d * c.d * CONV_K + c.d) * CONV_CHUNKS);
     for (int l = 1; l <= c.nl; ++l) a[l] = cv.take<float>((size_t)B * c.d * c.len[l]);
     const int64_t top = c.nl ? c.len[1] : c.len[0];
     h = cv.take<float>((size_t)B * c.hidden);
@@ -1035,7 +1163,7 @@ static void conv_in(const ConvShape& c, const float* u, const ConvPass& w, int l
 }
 
 static crom_status conv_encoder_fwd(const ConvShape& c, const float* prm, const float* u, int B, ConvPass& w,
-                                    hipStream_t st) {
+                                    float* q_out, hipStream_t st) {
   for (int l = 0; l < c.nl; ++l) {
     const float* x;
     int64_t xb, xc, xi;
@@ -1046,11 +1174,8 @@ static crom_status conv_encoder_fwd(const ConvShape& c, const float* prm, const 
   // the flattened top: [B][d][L] is [B][L d] channel-major; with no
   // convolution the snapshot itself ([B][P d], point-major)
   const float* flat = c.nl ? w.a[c.nl] : u;
-  const int64_t n_flat = c.len[c.nl] * c.d;
-  hipLaunchKernelGGL(dense_fwd_kernel, dim3(grid_for((int64_t)B * c.hidden)), dim3(256), 0, st, flat, prm + c.e1,
-                     prm + c.c1, B, n_flat, c.hidden, 1, w.h);
-  hipLaunchKernelGGL(dense_fwd_kernel, dim3(grid_for((int64_t)B * c.r)), dim3(256), 0, st, w.h, prm + c.e2,
-                     prm + c.c2, B, (int64_t)c.hidden, c.r, 0, w.q);
+  hipLaunchKernelGGL(dense_fwd_kernel, dim3((unsigned)B), dim3(256), 0, st, flat, prm + c.e1, prm + c.c1, prm + c.e2,
+                     prm + c.c2, c.len[c.nl] * c.d, c.hidden, c.r, w.h, w.q, q_out);
   return hip_check(hipGetLastError(), "convolutional encoder forward");
 }
 
@@ -1059,31 +1184,26 @@ static crom_status conv_encoder_bwd(const ConvShape& c, const float* prm, const 
   const float* flat = c.nl ? w.a[c.nl] : u;
   const int64_t n_flat = c.len[c.nl] * c.d;
   // last layer: dE2, dc2; dh = (dq E2) ELU'(h)
-  hipLaunchKernelGGL(dense_wgrad_kernel, dim3(grid_for((int64_t)c.r * c.hidden + c.r)), dim3(256), 0, st, dq, w.h, B,
-                     (int64_t)c.hidden, c.r, grad + c.e2, grad + c.c2);
-  hipLaunchKernelGGL(dense_dx_kernel, dim3(grid_for((int64_t)B * c.hidden)), dim3(256), 0, st, dq, prm + c.e2, w.h, B,
-                     (int64_t)c.hidden, c.r, w.dh);
+  hipLaunchKernelGGL(dense_bwd_kernel, dim3(grid_for((int64_t)(c.r + B) * c.hidden + c.r)), dim3(256), 0, st, dq, w.h,
+                     prm + c.e2, w.h, B, (int64_t)c.hidden, c.r, grad + c.e2, grad + c.c2, w.dh);
   // dense layer: dE1, dc1; the top convolution's output gradient
-  hipLaunchKernelGGL(dense_wgrad_kernel, dim3(grid_for((int64_t)c.hidden * n_flat + c.hidden)), dim3(256), 0, st, w.dh,
-                     flat, B, n_flat, c.hidden, grad + c.e1, grad + c.c1);
+  hipLaunchKernelGGL(dense_bwd_kernel, dim3(grid_for((int64_t)(c.hidden + B) * n_flat + c.hidden)), dim3(256), 0, st,
+                     w.dh, flat, prm + c.e1, c.nl ? w.a[c.nl] : nullptr, B, n_flat, c.hidden, grad + c.e1, grad + c.c1,
+                     c.nl ? w.dz[0] : nullptr);
   if (c.nl == 0) return hip_check(hipGetLastError(), "convolutional encoder backward");
-  hipLaunchKernelGGL(dense_dx_kernel, dim3(grid_for((int64_t)B * n_flat)), dim3(256), 0, st, w.dh, prm + c.e1,
-                     w.a[c.nl], B, n_flat, c.hidden, w.dz[0]);
+  const int nwb = c.d * c.d * CONV_K + c.d;  // a convolution's weights and biases, adjacent in the parameters
   int cur = 0;
   for (int l = c.nl - 1; l >= 0; --l) {  // convolution l: len[l] -> len[l + 1]
     const float* x;
     int64_t xb, xc, xi;
     conv_in(c, u, w, l, &x, &xb, &xc, &xi);
-    hipLaunchKernelGGL(conv_wgrad_kernel, dim3(c.d * c.d * CONV_K + c.d, CONV_CHUNKS), dim3(CONV_RED), 0, st,
-                       w.dz[cur], x, xb, xc, xi, B, c.d, c.len[l + 1], w.wpart);
-    hipLaunchKernelGGL(conv_wgrad_final_kernel, dim3(1), dim3(64), 0, st, w.wpart, c.d, grad + c.w[l],
-                       grad + c.b[l]);
-    if (l > 0) {
-      hipLaunchKernelGGL(conv_dx_kernel, dim3(grid_for((int64_t)B * c.d * c.len[l])), dim3(256), 0, st, w.dz[cur],
-                         prm + c.w[l], w.a[l], B, c.d, c.len[l], c.len[l + 1], w.dz[1 - cur]);
-      cur = 1 - cur;
-    }
+    const unsigned dx_blocks = l > 0 ? grid_for((int64_t)B * c.d * c.len[l]) : 0;
+    hipLaunchKernelGGL(conv_bwd_kernel, dim3(nwb * CONV_CHUNKS + dx_blocks), dim3(CONV_RED), 0, st, w.dz[cur], x, xb, xc,
+                       xi, prm + c.w[l], l > 0 ? w.a[l] : nullptr, B, c.d, c.len[l], c.len[l + 1],
+                       w.wpart + (size_t)l * nwb * CONV_CHUNKS, w.dz[1 - cur]);
+    cur = 1 - cur;
   }
+  hipLaunchKernelGGL(conv_wgrad_final_kernel, dim3(c.nl), dim3(64), 0, st, w.wpart, nwb, grad);
   return hip_check(hipGetLastError(), "convolutional encoder backward");
 }
 
@@ -1130,25 +1250,19 @@ static crom_status train_grads_t(const crom_net* n, const crom_encoder* e, const
     const ConvShape c = conv_of(n, e);
     ConvPass cp;
     cp.carve(cv, c, B);
-    crom_status s = conv_encoder_fwd(c, e->params, u, B, cp, st);
+    crom_status s = conv_encoder_fwd(c, e->params, u, B, cp, q_out, st);
     if (s != CROM_OK) return s;
     s = decoder_fwd_bwd<T>(n, x, B, P, cp.q, u, nullptr, grad_dec, cp.dq, loss, d, st);
     if (s != CROM_OK) return s;
-    s = conv_encoder_bwd(c, e->params, u, B, cp.dq, grad_enc, cp, st);
-    if (s != CROM_OK) return s;
-    if (q_out) s = hip_check(hipMemcpyAsync(q_out, cp.q, sizeof(float) * B * e->r, hipMemcpyDeviceToDevice, st), "q copy");
-    return s;
+    return conv_encoder_bwd(c, e->params, u, B, cp.dq, grad_enc, cp, st);
   }
   EncoderPass<T> en;
   en.carve(cv, e, B);
-  crom_status s = encoder_fwd<T>(e, u, B, en, st);
+  crom_status s = encoder_fwd<T>(e, u, B, en, q_out, st);
   if (s != CROM_OK) return s;
   s = decoder_fwd_bwd<T>(n, x, B, P, en.q, u, nullptr, grad_dec, en.dq, loss, d, st);
   if (s != CROM_OK) return s;
-  s = encoder_bwd<T>(e, B, en.dq, grad_enc, en, d.part, st);
-  if (s != CROM_OK) return s;
-  if (q_out) s = hip_check(hipMemcpyAsync(q_out, en.q, sizeof(float) * B * e->r, hipMemcpyDeviceToDevice, st), "q copy");
-  return s;
+  return encoder_bwd<T>(e, u, B, en.dq, grad_enc, en, st);
 }
 
 }  // namespace crom
@@ -1319,19 +1433,16 @@ crom_status crom_encode(const crom_net* net, const crom_encoder* enc, const floa
     const ConvShape c = conv_of(net, enc);
     ConvPass cp;
     cp.carve(cv, c, B);
-    if ((s = conv_encoder_fwd(c, enc->params, u, B, cp, st)) != CROM_OK) return s;
-    return hip_check(hipMemcpyAsync(q, cp.q, sizeof(float) * B * enc->r, hipMemcpyDeviceToDevice, st), "q copy");
+    return conv_encoder_fwd(c, enc->params, u, B, cp, q, st);
   }
   if (bf_mode(net)) {
     EncoderPass<__bf16> en;
     en.carve(cv, enc, B);
-    if ((s = encoder_fwd<__bf16>(enc, u, B, en, st)) != CROM_OK) return s;
-    return hip_check(hipMemcpyAsync(q, en.q, sizeof(float) * B * enc->r, hipMemcpyDeviceToDevice, st), "q copy");
+    return encoder_fwd<__bf16>(enc, u, B, en, q, st);
   }
   EncoderPass<float> en;
   en.carve(cv, enc, B);
-  if ((s = encoder_fwd<float>(enc, u, B, en, st)) != CROM_OK) return s;
-  return hip_check(hipMemcpyAsync(q, en.q, sizeof(float) * B * enc->r, hipMemcpyDeviceToDevice, st), "q copy");
+  return encoder_fwd<float>(enc, u, B, en, q, st);
 }
 
 crom_status crom_decode_vjp_workspace(const crom_net* net, int32_t B, int64_t P, size_t* bytes) {

@@ -532,8 +532,9 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
   }
 }
 
-// Sums the workgroups' partials in order (4 interleaved lanes per output,
-// then the lanes): blocks [0, nb_w) the layers' dW and db, then dWout, dbout
+// Sums the workgroups' partials in order (16 interleaved lanes per output,
+// then the lanes; four lanes kept too few loads in flight: 28 us for the 67 MB
+// of 256 workgroups): blocks [0, nb_w) the layers' dW and db, then dWout, dbout
 // and the loss, then S[seg][3][W] from the chunks.
 struct FusedReduceArgs {
   const float* part;
@@ -546,9 +547,16 @@ struct FusedReduceArgs {
   double* S;
   int segs;
 };
-__global__ __launch_bounds__(256) void fused_reduce_kernel(FusedReduceArgs a) {
-  __shared__ double sh[4][64];
-  const int t = threadIdx.x & 63, l4 = threadIdx.x >> 6;
+constexpr int TF_LANES = 16;
+__global__ __launch_bounds__(TF_LANES * 64) void fused_reduce_kernel(FusedReduceArgs a) {
+  __shared__ double sh[TF_LANES][64];
+  const int t = threadIdx.x & 63, lane = threadIdx.x >> 6;
+  auto total = [&](auto* v) {  // the lanes' sums of output t, in order
+    auto s = v[t];
+#pragma unroll
+    for (int l = 1; l < TF_LANES; ++l) s += v[64 * l + t];
+    return s;
+  };
   const int nb_w = a.L * TF_MAT / 64, nb_o = (TF_W + 2 + 63) / 64;
   const int blk = blockIdx.x;
   if (blk < nb_w) {  // FP32 partials, summed in FP32
@@ -557,27 +565,27 @@ __global__ __launch_bounds__(256) void fused_reduce_kernel(FusedReduceArgs a) {
     const size_t stride = (size_t)a.L * TF_MAT;
     float s = 0.0f;
 #pragma unroll 8
-    for (int z = l4; z < a.wgs; z += 4) s += a.part[z * stride + e];
-    shf[l4 * 64 + t] = s;
+    for (int z = lane; z < a.wgs; z += TF_LANES) s += a.part[z * stride + e];
+    shf[lane * 64 + t] = s;
     __syncthreads();
     if (threadIdx.x < 64)
       a.grad[(i < TF_W * TF_W ? a.pi.w[1 + l] + i : a.pi.b[1 + l] + i - TF_W * TF_W)] =
-          ((shf[t] + shf[64 + t]) + shf[128 + t]) + shf[192 + t];
+          total(shf);
     return;
   }
   double s = 0.0;
   if (blk < nb_w + nb_o) {
     const int o = (blk - nb_w) * 64 + t;
     if (o < TF_W + 2) {
-      for (int z = l4; z < a.wgs; z += 4) {
+      for (int z = lane; z < a.wgs; z += TF_LANES) {
         const double* p = a.opart + (size_t)z * (2 * TF_W + 2);
         s += o < TF_W ? p[o] + p[TF_W + o] : p[TF_W + o];
       }
     }
-    sh[l4][t] = s;
+    sh[lane][t] = s;
     __syncthreads();
     if (threadIdx.x < 64 && o < TF_W + 2) {
-      s = ((sh[0][t] + sh[1][t]) + sh[2][t]) + sh[3][t];
+      s = total(&sh[0][0]);
       if (o < TF_W) a.grad[a.pi.w[a.L + 1] + o] = (float)s;
       else if (o == TF_W) a.grad[a.pi.b[a.L + 1]] = (float)s;
       else if (a.loss) *a.loss = (float)(s / a.n);
@@ -587,10 +595,10 @@ __global__ __launch_bounds__(256) void fused_reduce_kernel(FusedReduceArgs a) {
   const int i = (blk - nb_w - nb_o) * 64 + t, seg = i / (3 * TF_W), o = i % (3 * TF_W);  // 3 W is a multiple of 64
   const double* p = a.spart + (size_t)seg * a.chunks * 3 * TF_W + o;
 #pragma unroll 8
-  for (int ch = l4; ch < a.chunks; ch += 4) s += p[(size_t)ch * 3 * TF_W];
-  sh[l4][t] = s;
+  for (int ch = lane; ch < a.chunks; ch += TF_LANES) s += p[(size_t)ch * 3 * TF_W];
+  sh[lane][t] = s;
   __syncthreads();
-  if (threadIdx.x < 64) a.S[i] = ((sh[0][t] + sh[1][t]) + sh[2][t]) + sh[3][t];
+  if (threadIdx.x < 64) a.S[i] = total(&sh[0][0]);
 }
 
 }  // namespace crom
