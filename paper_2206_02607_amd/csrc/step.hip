@@ -1359,6 +1359,7 @@ __device__ void solve_instance(const StepArgs& a, char* lds, int inst, int p, bo
       for (int u = 0; u < UNR; ++u) acc += (base + u * NS < b1) ? v[u] : 0.0;
     }
     sub[sl * NRED + e] = acc;
+    if constexpr (NTH == 0) break;  // a thread per entry and subset
   }
   __syncthreads();
   if (p == 1) trace_solve(a, 48);
