@@ -129,6 +129,11 @@ crom_status crom_net_pack(const crom_net* net, void* packed, void* stream);
 crom_status crom_decode(const crom_net* net, const float* x, int64_t P, const double* q,
                         float* g, void* stream);
 
+/* The same for B latents at shared points, in one launch: q [B][r],
+ * g [B][P][d].  B >= 0. */
+crom_status crom_decode_batch(const crom_net* net, const float* x, int64_t P, const double* q, int32_t B,
+                              float* g, void* stream);
+
 /* Values with any subset of the derivative columns, all from one forward
  * pass of value and tangents through the layers (Alg. "Network gradient",
  * extended to second order in x and to the latent directions):

@@ -1,5 +1,5 @@
 """torch.autograd.Function over the decoder: forward by the fused decode
-kernel (crom_decode, one call per latent), backward by crom_decode_vjp (the
+kernel (crom_decode_batch, every latent in one launch), backward by crom_decode_vjp (the
 hand-written reverse-mode kernels, activations recomputed)."""
 from __future__ import annotations
 
@@ -18,11 +18,8 @@ class DecodeFunction(torch.autograd.Function):
     def forward(ctx, params, q, x, dec: Decoder):
         if params.data_ptr() != dec.params.data_ptr():
             raise CromError("params must be the decoder's own parameter tensor")
-        B, P = q.shape[0], x.shape[0]
-        out = torch.empty(B, P, dec.d, dtype=torch.float32, device=x.device)
         xc = x.to(torch.float32).contiguous()
-        for b in range(B):
-            dec.decode(xc, q[b].detach(), out=out[b])
+        out = dec.decode_batch(xc, q.detach())
         ctx.save_for_backward(q, xc)
         ctx.dec = dec
         return out

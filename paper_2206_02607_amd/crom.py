@@ -97,6 +97,7 @@ def lib():
         L.crom_net_packed_bytes.argtypes = [POINTER(CromNet)]
         L.crom_net_pack.argtypes = [POINTER(CromNet), c_void_p, c_void_p]
         L.crom_decode.argtypes = [POINTER(CromNet), c_void_p, c_int64, c_void_p, c_void_p, c_void_p]
+        L.crom_decode_batch.argtypes = [POINTER(CromNet), c_void_p, c_int64, c_void_p, c_int32, c_void_p, c_void_p]
         L.crom_decode_jac.argtypes = [POINTER(CromNet), c_void_p, c_int64, c_void_p, c_int32,
                                       c_void_p, c_void_p, c_void_p, c_void_p, c_void_p]
         L.crom_decode_jac_x.argtypes = [POINTER(CromNet), c_void_p, c_int64, c_void_p, c_int32,
@@ -183,7 +184,7 @@ def lib():
                      "crom_fold_standardization", "crom_train_state_offsets", "crom_train_step_state",
                      "crom_step_static", "crom_heat_fallback_workspace", "crom_heat_fallback"):
             getattr(L, name).restype = c_int32
-        for name in ("crom_net_pack", "crom_decode", "crom_decode_jac", "crom_decode_jac_x",
+        for name in ("crom_net_pack", "crom_decode", "crom_decode_batch", "crom_decode_jac", "crom_decode_jac_x",
                      "crom_decode_jac_q", "crom_step_workspace", "crom_step", "crom_fd_heat",
                      "crom_train_workspace", "crom_train_grads", "crom_adam_step", "crom_train_step",
                      "crom_decode_vjp_workspace", "crom_decode_vjp", "crom_encode_workspace",
@@ -282,6 +283,22 @@ class Decoder:
         g = out if out is not None else torch.empty(P, self.d, dtype=torch.float32, device=x.device)
         net = self._net()
         _check(lib().crom_decode(ctypes.byref(net), _ptr(x), P, _ptr(q), _ptr(g), _stream()), "crom_decode")
+        return g
+
+    def decode_batch(self, x, q):
+        """Values [B, P, d] at the points x [P, m] for latents q [B, r] (one launch)."""
+        torch = _torch()
+        x = x.to(dtype=torch.float32).contiguous()
+        q = q.to(device=x.device, dtype=torch.float64).contiguous()
+        B, P = q.shape[0], x.shape[0]
+        g = torch.empty(B, P, self.d, dtype=torch.float32, device=x.device)
+        if B == 0:
+            return g
+        if x.dim() != 2 or x.shape[1] != self.m or q.numel() != B * self.r:
+            raise CromError("x must be [P, m] and q [B, r]")
+        net = self._net()
+        _check(lib().crom_decode_batch(ctypes.byref(net), _ptr(x), P, _ptr(q), B, _ptr(g), _stream()),
+               "crom_decode_batch")
         return g
 
     def decode_jac(self, x, q, dx=True, d2=D2_NONE, dq=True):

@@ -5,6 +5,7 @@
 
 #include <vector>
 
+#include "chain.hpp"
 #include "common.hpp"
 #include "tune.hpp"
 
@@ -114,7 +115,8 @@ static size_t packed_bytes(int w, int depth, int prec) {
 struct DecodeArgs {
   const float* x;
   int64_t P;
-  const double* q;
+  const double* q;   // [B][r]
+  int B;             // latents (values only; else 1)
   const float* params;
   const char* packed;
   ParamIndex pi;
@@ -133,12 +135,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
   float* par = reinterpret_cast<float*>(lds + E::LDS_BYTES);
   E::PC::load(par, a.params, a.pi, a.depth, E::THREADS);  // once for all of this workgroup's batches
   __syncthreads();
+  // the batch's latent and values (locals: a written kernel argument is copied
+  // to scratch, parameter index and all, 4 us)
+  const double* const q = a.q + blockIdx.y * S::R;
+  float* const g = a.g + blockIdx.y * a.P * S::D;
   const int64_t nbatch = (a.P + E::NPTS - 1) / E::NPTS;
   for (int64_t bi = blockIdx.x; bi < nbatch; bi += gridDim.x) {
   const int64_t first = bi * E::NPTS;
   const int64_t rem = a.P - first;
   const int n_valid = rem < E::NPTS ? (int)rem : E::NPTS;
-  E::stage(lds, a.x, first, n_valid, a.q, S::R, nullptr, 0, par);
+  E::stage(lds, a.x, first, n_valid, q, S::R, nullptr, 0, par);
   __syncthreads();
   E::run(lds, par, a.packed, a.depth, a.qb);
   const float* res = reinterpret_cast<const float*>(lds + E::RES_OFF);
@@ -155,7 +161,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
     const float v = res[i];
     const int k = C::kind(c);
     if (k == CK_VAL) {
-      a.g[p * D + oo] = v;
+      g[p * D + oo] = v;
     } else if (k == CK_XT) {
       if (a.dgdx) a.dgdx[(p * D + oo) * M + (c - C::X0)] = v;
     } else if (k == CK_LAP) {
@@ -170,10 +176,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
   }
 }
 
-template <class S, class C, int NB, int PREC>
+template <class S, class C, int NB, int PREC, class T = DecodeTune<S, PREC>>
 static crom_status launch_decode(const DecodeArgs& a, hipStream_t st) {
-  using T = DecodeTune<S, PREC>;
-  constexpr int NW = T::NW;
+  constexpr int NW = DecodeTune<S, PREC>::NW;
   using E = Engine<S, C, NB, NW, PREC, T::PF>;
   const int lds_bytes = E::LDS_BYTES + E::PC::bytes(a.depth);
   if (lds_bytes > LDS_MAX) {
@@ -190,10 +195,43 @@ static crom_status launch_decode(const DecodeArgs& a, hipStream_t st) {
     if (blocks > 0x7fffffff) return fail(CROM_ERR_INVALID_ARG, "P too large");
     // a few workgroups per CU, each looping over batches with its parameter
     // cache loaded once
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(E::THREADS), lds_bytes, st, a);
+    const int64_t cap = a.B < 4096 ? 4096 / a.B : 1;
+    if (blocks > cap) blocks = cap;
+    hipLaunchKernelGGL(k, dim3((unsigned)blocks, (unsigned)a.B), dim3(E::THREADS), lds_bytes, st, a);
     return hip_check(hipGetLastError(), "decode launch");
   }
+}
+
+// Value decode with the activations in registers (chain.hpp).
+template <class S>
+__global__ __launch_bounds__(Chain<S>::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void decode_chain_kernel(
+    DecodeArgs a, ChainPlan plan) {
+  extern __shared__ __align__(16) char lds[];
+  struct {
+    float* g;
+    int64_t P;
+    float v;
+    __device__ void begin() {}
+    __device__ void load(int64_t, int, int64_t) {}
+    __device__ void take(float value) { v = value; }
+    __device__ void store(int64_t set, int64_t p) { g[set * P + p] = v; }
+  } sink{a.g, a.P, 0.0f};
+  chain_sweep<S>(lds, a.params, a.pi, a.packed, a.depth, a.x, a.P, a.q, 1, plan, sink);
+}
+
+template <class S>
+static crom_status launch_chain(const DecodeArgs& a, hipStream_t st) {
+  using C = Chain<S>;
+  auto k = decode_chain_kernel<S>;
+  static bool attr = false;
+  if (!attr) {
+    crom_status s = set_lds(k, LDS_MAX);
+    if (s != CROM_OK) return s;
+    attr = true;
+  }
+  const ChainPlan plan = ChainPlan::of(a.P, a.B, C::CUS);
+  hipLaunchKernelGGL(k, dim3((unsigned)plan.blocks), dim3(C::THREADS), C::lds_bytes(a.depth), st, a, plan);
+  return hip_check(hipGetLastError(), "decode launch");
 }
 
 // FP32 with the latent Jacobian by the reverse pass (RevJets): the forward
@@ -275,7 +313,10 @@ template <class S, int NW, int PREC, bool XT, int D2, int NQ, int HB = 0,
 static crom_status run_pass(const DecodeArgs& a, hipStream_t st) {
   if constexpr (!XT && D2 == D2_NONE && NQ == 0) {
     using C = Cols<S::M, S::R, 1, 0, false, D2_NONE, 0>;
-    return launch_decode<S, C, DecodeTune<S, PREC>::NBV, PREC>(a, st);
+    if constexpr (S::W == 128 && PREC == PREC_BF16) {
+      if (chain_takes<S>(a.depth, a.P, a.B)) return launch_chain<S>(a, st);
+    }
+    return launch_decode<S, C, DecodeTune<S, PREC>::NBV, PREC, ValueTune<S, PREC>>(a, st);
   } else {
     using C = Cols<S::M, S::R, 1, 0, XT, D2, NQ, HB, NH>;
     return launch_decode<S, C, 1, PREC>(a, st);
@@ -374,7 +415,7 @@ static crom_status decode_prec(int prec, const DecodeArgs& a, bool xt, int d2, b
   }
 }
 
-static crom_status decode_any(const crom_net* net, const float* x, int64_t P, const double* q,
+static crom_status decode_any(const crom_net* net, const float* x, int64_t P, const double* q, int B,
                               int d2_mode, float* g, float* dgdx, float* d2g, float* dgdq,
                               void* stream) {
   crom_status s = check_net(net, true);
@@ -392,6 +433,7 @@ static crom_status decode_any(const crom_net* net, const float* x, int64_t P, co
   a.x = x;
   a.P = P;
   a.q = q;
+  a.B = B;
   a.params = net->params;
   a.packed = static_cast<const char*>(net->packed);
   a.pi = param_index(net->m, net->r, net->d, net->width, net->depth);
@@ -505,24 +547,38 @@ crom_status crom_net_pack(const crom_net* net, void* packed, void* stream) {
 
 crom_status crom_decode(const crom_net* net, const float* x, int64_t P, const double* q, float* g,
                         void* stream) {
-  return decode_any(net, x, P, q, CROM_D2_NONE, g, nullptr, nullptr, nullptr, stream);
+  return decode_any(net, x, P, q, 1, CROM_D2_NONE, g, nullptr, nullptr, nullptr, stream);
+}
+
+crom_status crom_decode_batch(const crom_net* net, const float* x, int64_t P, const double* q, int32_t B, float* g,
+                              void* stream) {
+  if (B < 0) return crom::fail(CROM_ERR_INVALID_ARG, "B < 0");
+  if (B == 0) return decode_any(net, x, 0, q, 1, CROM_D2_NONE, g, nullptr, nullptr, nullptr, stream);
+  constexpr int CHUNK = 32768;  // the grid's second dimension
+  for (int32_t b = 0; b < B; b += CHUNK) {
+    const int n = B - b < CHUNK ? B - b : CHUNK;
+    crom_status s = decode_any(net, x, P, q ? q + (size_t)b * net->r : q, n, CROM_D2_NONE,
+                               g ? g + (size_t)b * P * net->d : g, nullptr, nullptr, nullptr, stream);
+    if (s != CROM_OK) return s;
+  }
+  return CROM_OK;
 }
 
 crom_status crom_decode_jac(const crom_net* net, const float* x, int64_t P, const double* q,
                             int32_t d2_mode, float* g, float* dgdx, float* d2g, float* dgdq,
                             void* stream) {
-  return decode_any(net, x, P, q, d2_mode, g, dgdx, d2g, dgdq, stream);
+  return decode_any(net, x, P, q, 1, d2_mode, g, dgdx, d2g, dgdq, stream);
 }
 
 crom_status crom_decode_jac_x(const crom_net* net, const float* x, int64_t P, const double* q,
                               int32_t d2_mode, float* g, float* dgdx, float* d2g, void* stream) {
-  return decode_any(net, x, P, q, d2_mode, g, dgdx, d2g, nullptr, stream);
+  return decode_any(net, x, P, q, 1, d2_mode, g, dgdx, d2g, nullptr, stream);
 }
 
 crom_status crom_decode_jac_q(const crom_net* net, const float* x, int64_t P, const double* q,
                               float* g, float* dgdq, void* stream) {
   if (P > 0 && !dgdq) return crom::fail(CROM_ERR_INVALID_ARG, "dgdq is required");
-  return decode_any(net, x, P, q, CROM_D2_NONE, g, nullptr, nullptr, dgdq, stream);
+  return decode_any(net, x, P, q, 1, CROM_D2_NONE, g, nullptr, nullptr, dgdq, stream);
 }
 
 }  // extern "C"

@@ -8,6 +8,7 @@
 
 #include <vector>
 
+#include "chain.hpp"
 #include "common.hpp"
 #include "tune.hpp"
 
@@ -76,12 +77,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
 
 template <class S, int PREC>
 static crom_status launch_residual(const ResidualArgs& a, int n_set, hipStream_t st) {
-  using T = DecodeTune<S, PREC>;
+  constexpr int NW = DecodeTune<S, PREC>::NW;
+  using T = ValueTune<S, PREC>;
   using C = Cols<S::M, S::R, 1, 0, false, D2_NONE, 0>;
-  using E = Engine<S, C, 4, T::NW, PREC, T::PF>;
+  using E = Engine<S, C, 4, NW, PREC, T::PF>;
   const int lds_bytes = E::LDS_BYTES + E::PC::bytes(a.depth);
   if (lds_bytes > LDS_MAX) return fail(CROM_ERR_UNSUPPORTED, "network too deep for the LDS");
-  auto k = residual_kernel<S, T::NW, PREC, T::PF, T::WPE>;
+  auto k = residual_kernel<S, NW, PREC, T::PF, T::WPE>;
   static bool attr = false;
   if (!attr) {
     crom_status s = set_lds(k, LDS_MAX);
@@ -98,11 +100,52 @@ static crom_status launch_residual(const ResidualArgs& a, int n_set, hipStream_t
   return hip_check(hipGetLastError(), "residual launch");
 }
 
+// The same with the activations in registers (chain.hpp): an item of points
+// keeps its norms through the latents of its set.
+template <class S>
+__global__ __launch_bounds__(Chain<S>::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void residual_chain_kernel(
+    ResidualArgs a, ChainPlan plan) {
+  extern __shared__ __align__(16) char lds[];
+  struct {
+    const double* ref;
+    double* res;
+    int64_t P;
+    double acc, f;
+    __device__ void begin() { acc = 0.0; }
+    __device__ void load(int64_t, int k, int64_t p) { f = ref[k * P + p]; }
+    __device__ void take(float value) {
+      const double e = (double)value - f;
+      acc += sqrt(e * e);
+    }
+    __device__ void store(int64_t set, int64_t p) { res[set * P + p] = acc; }
+  } sink{a.ref, a.res, a.P, 0.0, 0.0};
+  chain_sweep<S>(lds, a.params, a.pi, a.packed, a.depth, a.x, a.P, a.q, a.n_mu, plan, sink);
+}
+
+template <class S>
+static crom_status launch_residual_chain(const ResidualArgs& a, int n_set, hipStream_t st) {
+  using C = Chain<S>;
+  auto k = residual_chain_kernel<S>;
+  static bool attr = false;
+  if (!attr) {
+    crom_status s = set_lds(k, LDS_MAX);
+    if (s != CROM_OK) return s;
+    attr = true;
+  }
+  const ChainPlan plan = ChainPlan::of(a.P, n_set, C::CUS);
+  hipLaunchKernelGGL(k, dim3((unsigned)plan.blocks), dim3(C::THREADS), C::lds_bytes(a.depth), st, a, plan);
+  return hip_check(hipGetLastError(), "residual launch");
+}
+
 template <class S>
 static crom_status residual_prec(int prec, const ResidualArgs& a, int n_set, hipStream_t st) {
   switch (prec) {
     case CROM_PREC_FP32: return launch_residual<S, PREC_FP32>(a, n_set, st);
-    case CROM_PREC_BF16: return launch_residual<S, PREC_BF16>(a, n_set, st);
+    case CROM_PREC_BF16:
+      if constexpr (S::W == 128 && S::D == 1) {
+        if (chain_takes<S>(a.depth, a.P, n_set)) return launch_residual_chain<S>(a, n_set, st);
+      }
+      return launch_residual<S, PREC_BF16>(a, n_set, st);
     case CROM_PREC_BF16_PURE: return launch_residual<S, PREC_BF16_PURE>(a, n_set, st);
     default: return launch_residual<S, PREC_BF16X3>(a, n_set, st);
   }

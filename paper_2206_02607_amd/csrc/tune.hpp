@@ -16,9 +16,10 @@ namespace crom {
 // 4 waves (two M-tiles each, so every activation fragment read from LDS
 // feeds two products) with streamed fragments held to 256 registers 633
 // (two workgroups per CU); 2 waves 488.
-// NBV: 16-point batches per workgroup of the value-only (full-field)
-// decode.  2D BF16, 65,536 points: 32 per workgroup 36.3 us, 64 35.0 us,
-// 128 32.1 us (FP32: 96.3, 86.2, 90.2 us).
+// NBV: 16-point batches per workgroup of the value-only decode.  2D FP32,
+// 65,536 points: 32 per workgroup 96.3 us, 64 86.2 us, 128 90.2 us.  2D BF16,
+// 1,000, 16,384 and 49,152 points: 64 per workgroup 13.4, 13.8 and 21.4 us, 128
+// 20.1, 20.1 and 25.0 us; more points than that are Chain's.
 template <class S, int PREC>
 struct DecodeTune {
   static constexpr int NW = S::W <= 32 ? 2 : (S::W <= 128 ? 4 : 8);
@@ -28,7 +29,7 @@ struct DecodeTune {
 };
 template <>
 struct DecodeTune<Shape<128, 2, 8, 1>, PREC_BF16> {
-  static constexpr int NW = 4, PF = 2, WPE = 2, NBV = 8;
+  static constexpr int NW = 4, PF = 2, WPE = 2, NBV = 4;
 };
 template <>
 struct DecodeTune<Shape<128, 2, 8, 1>, PREC_BF16_PURE> {
@@ -37,6 +38,16 @@ struct DecodeTune<Shape<128, 2, 8, 1>, PREC_BF16_PURE> {
 template <>
 struct DecodeTune<Shape<128, 2, 8, 1, ACT_SINE>, PREC_BF16> {
   static constexpr int NW = 4, PF = 2, WPE = 2, NBV = 4;
+};
+
+// Values of 128-wide networks in BF16 mode (where Chain does not take them):
+// the launch shape measured for the 2D decoder, with 16 latent values too
+// (16,385 points 25.7 -> 15.5 us, 65,537 points 61.6 -> 32 us).
+template <class S, int PREC>
+struct ValueTune {
+  using T = DecodeTune<S, PREC>;
+  static constexpr bool W128 = S::W == 128 && S::D == 1 && PREC == PREC_BF16;
+  static constexpr int PF = W128 ? 2 : T::PF, WPE = W128 ? 2 : T::WPE;
 };
 
 }  // namespace crom

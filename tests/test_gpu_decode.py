@@ -177,3 +177,44 @@ def test_fp32_jacobian_paths(cuda, shape, depth, P, dx, d2):
         assert (a is None) == (b is None)
         if a is not None:
             assert normwise_rel(a.cpu().numpy().reshape(b.shape), b) <= TOL["fp32"]
+
+
+# Value decode of many points at width 128 in BF16 (activations in registers):
+# the same products, sums and epilogues in the same order as the kernel that
+# small calls use, so the values are the same bits; batches (B latents) too.
+# Sizes at the edges: three and four of its 64-point batches per compute unit,
+# whole and cut last rounds of 256-point groups, ragged ends, 2 to 6 layers.
+@pytest.mark.parametrize("shape,act,depth,B,P", [
+    ("2d", "elu", 5, 1, 49153), ("2d", "elu", 5, 1, 65536), ("2d", "elu", 5, 1, 65537),
+    ("2d", "elu", 5, 1, 81920 + 129), ("2d", "elu", 2, 1, 99999), ("2d", "elu", 3, 1, 131072 + 30000),
+    ("2d", "elu", 6, 1, 99999), ("2d", "elu", 5, 1001, 61), ("2d", "elu", 4, 7, 20011), ("2d", "elu", 5, 3, 17),
+    ("2d_r16", "elu", 5, 2, 50011), ("2d", "sine", 5, 1, 65535), ("2d", "sine", 5, 5, 1001)])
+def test_decode_many_points(cuda, shape, act, depth, B, P):
+    import torch
+    from paper_2206_02607_amd import crom
+    m, r, d, w, _ = SHAPES[shape]
+    g = rng(31)
+    layers = xavier_mlp(g, m, r, d, w, depth, bias_scale=0.2)
+    dec = crom.Decoder.from_layers(layers, m, precision="bf16", device="cuda:0", act=act)
+    x = torch.from_numpy(uniform_points(g, P, m)).to(cuda)
+    q = torch.from_numpy(g.uniform(-1, 1, size=(B, r))).to(cuda)
+    got = dec.decode_batch(x, q)
+    assert got.shape == (B, P, d)
+    for b in range(0, B, max(1, B // 4)):
+        want = torch.cat([dec.decode(xs, q[b]) for xs in x.split(9973)])
+        assert torch.equal(got[b], want)
+
+
+def test_decode_batch_arguments(cuda):
+    import torch
+    from paper_2206_02607_amd import crom
+    layers, x, q, m = _case("2d", 5, 33)
+    dec = _decoder(layers, m, "fp32")
+    xt = torch.from_numpy(x).to(cuda)
+    q2 = torch.from_numpy(np.stack([q, 0.5 * q]).T.copy().T).to(cuda)  # strided
+    got = dec.decode_batch(xt, q2)
+    assert torch.equal(got[0], dec.decode(xt, q2[0])) and torch.equal(got[1], dec.decode(xt, q2[1]))
+    assert dec.decode_batch(xt, q2[:0]).shape == (0, 33, 1)
+    assert dec.decode_batch(xt[:0], q2).shape == (2, 0, 1)
+    with pytest.raises(crom.CromError):
+        dec.decode_batch(xt, q2[:, :7])

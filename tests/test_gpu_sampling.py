@@ -226,3 +226,25 @@ def test_elastic_residual_loop_runs(cuda):
     rel = np.abs(out.metrics[0] - mets) / mets
     print("elastic candidate metrics", mets, "error", rel.max())
     assert rel.max() <= 1e-3
+
+
+# Width 128 in BF16: a value is the decode's, bit for bit, and a node's norms
+# are added in the latents' order whichever kernel takes the call: few 64-node
+# batches per compute unit, and whole and cut last rounds of 256-node groups.
+@pytest.mark.parametrize("n_set,n_mu,P,r", [(1, 3, 1, 8), (2, 2, 333, 8), (4, 3, 16001, 8), (6, 2, 16384, 8),
+                                            (10, 2, 16384, 8), (600, 2, 70, 8), (5, 3, 12011, 16)])
+def test_residual_is_the_sum_of_decode_differences(cuda, n_set, n_mu, P, r):
+    import torch
+    from paper_2206_02607_amd import crom
+    g = rng(13)
+    layers = xavier_mlp(g, 2, r, 1, 128, 5, bias_scale=0.1)
+    dec = _dev_net(layers, 2, "bf16", cuda)
+    x = torch.from_numpy(uniform_points(g, P, 2).astype(np.float32)).to(cuda)
+    q = torch.from_numpy(g.uniform(-1, 1, size=(n_set, n_mu, r))).to(cuda)
+    ref = torch.from_numpy(g.standard_normal(size=(n_mu, P, 1))).to(cuda)
+    res, _ = crom.sampling_residual(dec, x, q, ref)
+    for s in range(0, n_set, max(1, n_set // 3)):
+        want = torch.zeros(P, dtype=torch.float64, device=cuda)
+        for k in range(n_mu):
+            want = want + (dec.decode(x, q[s, k]).to(torch.float64) - ref[k]).abs()[:, 0]
+        assert torch.equal(res[s], want)
