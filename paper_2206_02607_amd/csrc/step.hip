@@ -387,10 +387,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void setup_kernel(StepArgs a) {
     sync[SYNC_EXITED] = 0;
     act_phase[0] = n_active;
   }
-  for (int p = tid + 1; p < MAXP + 2; p += SETUP_THREADS) {
-    act_phase[p] = 0;
-    wsp<uint64_t>(a, a.L.work_cnt)[p] = 0;
-  }
+  for (int p = tid + 1; p < MAXP + 2; p += SETUP_THREADS) act_phase[p] = 0;
   for (int i = tid; i < a.n_inst; i += SETUP_THREADS) {
     inst_cnt[i] = 0;
     wsp<uint32_t>(a, a.L.inv)[i] = 0;
@@ -1469,7 +1466,7 @@ __device__ void solve_instance(const StepArgs& a, char* lds, int inst, int p, bo
         flags |= CROM_FLAG_NONFINITE;
         done = true;
       } else {
-        const CholOut o = NTH ? chol_solve_call<R>(red, bv) : chol_solve<R>(red, bv);
+        const CholOut o = NTH && LIST ? chol_solve_call<R>(red, bv) : chol_solve<R>(red, bv);
         const double xk = lane < R ? o.x : 0.0, dn = o.xx, sl = o.bx;
         double qq = 0.0;
 #pragma unroll
@@ -1662,7 +1659,7 @@ struct StepTraits<S, NW, PREC, PF, PK_ELASTIC> {
   static constexpr int PAR = JD_OFF + PT * S::D * (S::R + TV) * 8;
 };
 
-template <class S, int NW, int PREC, int PF, int KIND, int WPE, bool REV>
+template <class S, int NW, int PREC, int PF, int KIND, int WPE, bool REV, int NTH>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) void step_kernel(StepArgs a,
                                                                                           int max_rounds) {
   using T = StepTraits<S, NW, PREC, PF, KIND, REV>;
@@ -1754,7 +1751,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
       const bool last = s_last != 0;
       __syncthreads();  // every thread has read s_last before thread 0 may write it again
       if (p == 1 && w == blockIdx.x) trace_mark(a, 46);
-      if (last) solve_instance<S::R, LAZY>(a, lds, inst, p, p == max_rounds);
+      if (last) solve_instance<S::R, LAZY, NTH>(a, lds, inst, p, p == max_rounds);
       if (p == 1 && w == blockIdx.x) trace_mark(a, 47);
     }
     trace_mark(a, 4 * p + 1);
@@ -1946,9 +1943,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
   __shared__ double qdl[TV * RMAX];
   // Round p >= 1 evaluates the batches that the solves of round p - 1 listed
   // for their continuing instances (list p % 2, a count per round); this
-  // round's solves fill the other list.  Round 0 evaluates every batch.
+  // round's solves fill the other list.  Round 0 evaluates every batch and
+  // clears the counts (its solves run after this kernel on the same stream).
+  int64_t* work_cnt = wsp<int64_t>(a, a.L.work_cnt);
+  if (p == 0 && blockIdx.x == 0)
+    for (int i = threadIdx.x; i < MAXP + 2; i += NW * 64) work_cnt[i] = 0;
   if (ld_c(wsp<int64_t>(a, a.L.act_phase) + p) == 0) return;  // uniform: nothing active in this round
-  const int64_t nblk = p == 0 ? *wsp<int64_t>(a, a.L.nblk) : wsp<int64_t>(a, a.L.work_cnt)[p];
+  const int64_t nblk = p == 0 ? *wsp<int64_t>(a, a.L.nblk) : work_cnt[p];
   if ((int64_t)blockIdx.x >= nblk) return;
   const int32_t* list = wsp<int32_t>(a, a.L.work) + (int64_t)(p % 2) * a.L.nblk_max;
   float* par = reinterpret_cast<float*>(lds + T::PAR);
@@ -2195,7 +2196,7 @@ static crom_status fe_prepare(const StepArgs& a, hipStream_t st) {
   return hip_check(hipGetLastError(), "finite-element targets launch");
 }
 
-template <class S, int NW, int PREC, int PF, int KIND, int WPE, bool REV>
+template <class S, int NW, int PREC, int PF, int KIND, int WPE, bool REV, int NTH>
 static crom_status launch_step_t(StepArgs a, int max_rounds, hipStream_t st) {
   using T = StepTraits<S, NW, PREC, PF, KIND, REV>;
   constexpr int PAR = T::PAR;
@@ -2207,7 +2208,7 @@ static crom_status launch_step_t(StepArgs a, int max_rounds, hipStream_t st) {
                     (NW * 64 + S::R * (S::R + 1) / 2 + S::R + TV + S::R * S::R + S::R) * 8 <= PAR,
                 "solve scratch fits below the parameter cache");
   static_assert(NW * 64 >= S::R * (S::R + 1) / 2 + S::R + TV, "one thread per reduced entry");
-  auto k = step_kernel<S, NW, PREC, PF, KIND, WPE, REV>;
+  auto k = step_kernel<S, NW, PREC, PF, KIND, WPE, REV, NTH>;
   static int resident = 0, resident_lds = -1;
   if (resident_lds != lds_bytes) {
     crom_status s = set_lds(k, LDS_MAX - (int)sizeof(double) * TV * RMAX - 64);
@@ -2241,18 +2242,19 @@ static crom_status launch_step_t(StepArgs a, int max_rounds, hipStream_t st) {
   return s;
 }
 
-template <class S, int NW, int PREC, int PF, int KIND = PK_HEAT, int WPE = 1>
+template <class S, int NW, int PREC, int PF, int KIND = PK_HEAT, int WPE = 1, int NTH = 0>
 static crom_status launch_step(StepArgs a, int max_rounds, hipStream_t st) {
   if constexpr (KIND == PK_HEAT) {
     if (CROM_GN_REV && RevLap<S, NW, PREC, PF>::supported(a.depth))
-      return launch_step_t<S, NW, PREC, PF, KIND, WPE, true>(a, max_rounds, st);
+      return launch_step_t<S, NW, PREC, PF, KIND, WPE, true, NTH>(a, max_rounds, st);
   }
-  return launch_step_t<S, NW, PREC, PF, KIND, WPE, false>(a, max_rounds, st);
+  return launch_step_t<S, NW, PREC, PF, KIND, WPE, false, NTH>(a, max_rounds, st);
 }
 
 // Waves per workgroup and weight prefetch per precision, chosen so that the
 // persistent kernel stays clear of register spills: bfloat16 fragments are
-// half the size, so BF16 and BF16_PURE afford eight waves with prefetch.
+// half the size, so BF16 and BF16_PURE afford eight waves with prefetch.  NWF:
+// the waves of FP32's batch kernels and of BF16X3.
 template <class S, int NWB, int NWF, int PFB = 1, int WPEB = 1>
 static crom_status step_prec(int prec, const StepArgs& a, int rounds, hipStream_t st) {
   // sine networks: FP32 and BF16 only (checked by check_net)
@@ -2287,7 +2289,13 @@ static crom_status step_prec(int prec, const StepArgs& a, int rounds, hipStream_
     }
     return fail(CROM_ERR_UNSUPPORTED, "precision");
   }
-  if (prec == CROM_PREC_FP32) return launch_step<S, NWF, PREC_FP32, 0>(a, rounds, st);
+  if (prec == CROM_PREC_FP32) {
+    // eight waves at width 128: a batch's products are half as long (2D step of
+    // 40 samples 110 -> 101.5 us, of 1,000 112.5 -> 103), the solve's sums in
+    // the order of the rounds' four
+    constexpr int NWP = S::W == 128 && S::R <= 8 ? 8 : NWF;
+    return launch_step<S, NWP, PREC_FP32, 0, PK_HEAT, 1, (NWP == NWF ? 0 : NWF * 64)>(a, rounds, st);
+  }
   if (prec == CROM_PREC_BF16) return launch_step<S, NWB, PREC_BF16, PFB, PK_HEAT, WPEB>(a, rounds, st);
   if constexpr (ALL) {
     if (prec == CROM_PREC_BF16_PURE) return launch_step<S, NWB, PREC_BF16_PURE, PFB, PK_HEAT, WPEB>(a, rounds, st);
