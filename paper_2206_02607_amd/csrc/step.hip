@@ -317,13 +317,16 @@ __device__ __forceinline__ void trace_solve(const StepArgs&, int) {}
 #endif
 
 // ---------------------------------------------------------------------------
-// Block map and state initialisation (one workgroup of 1024 threads).
+// Block map and state initialisation.  Every workgroup scans all offsets (so
+// none waits for another) and fills the map and the state of its share of the
+// instances; the first one writes what there is once.
 // Offsets that are not a valid CSR array (a negative size, a range outside
 // [0, total]) give every instance zero batches; an instance without batches
 // ends at once as SINGULAR with q_{n+1} = q_n.  Valid CSR ranges are
 // disjoint, so the batch count stays within the bound the workspace was
 // sized for.  Up to SETUP_LDS instances the prefix and the offsets are kept
-// in LDS for the block fill; beyond that they are read back from memory.
+// in LDS for the block fill; beyond that they are read back from memory, by
+// the only workgroup.
 // ---------------------------------------------------------------------------
 constexpr int SETUP_THREADS = 1024;
 constexpr int SETUP_LDS = 2048;
@@ -336,13 +339,13 @@ __global__ __launch_bounds__(SETUP_THREADS) void setup_kernel(StepArgs a) {
   uint32_t* inst_cnt = wsp<uint32_t>(a, a.L.inst_cnt);
   uint64_t* sync = wsp<uint64_t>(a, a.L.sync);
   GNState* st = wsp<GNState>(a, a.L.state);
-  __shared__ int32_t scan[SETUP_THREADS];
+  __shared__ int32_t wave_sum[SETUP_THREADS / 64];
   __shared__ int32_t fb[SETUP_LDS + 1];
   __shared__ int64_t lo_off[SETUP_LDS];
   __shared__ int32_t carry;
   __shared__ int32_t n_active;
-  const int tid = threadIdx.x;
-  const bool in_lds = a.n_inst <= SETUP_LDS;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool in_lds = a.n_inst <= SETUP_LDS, once = blockIdx.x == 0;
   int bad = 0;
   for (int i = tid; i < a.n_inst; i += SETUP_THREADS) {
     const int64_t lo = a.offsets[i], hi = a.offsets[i + 1];
@@ -359,36 +362,44 @@ __global__ __launch_bounds__(SETUP_THREADS) void setup_kernel(StepArgs a) {
     const int i = c + tid;
     int32_t nb = 0;
     if (i < a.n_inst && !bad) nb = (int32_t)((a.offsets[i + 1] - a.offsets[i] + PT - 1) / PT);
-    scan[tid] = nb;
+    int32_t inc = nb;  // inclusive scan of the wave, then the waves' sums
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int32_t v = __shfl_up(inc, d);
+      inc += lane >= d ? v : 0;
+    }
+    if (lane == 63) wave_sum[wave] = inc;
     __syncthreads();
-    for (int d = 1; d < SETUP_THREADS; d <<= 1) {  // inclusive Hillis-Steele scan
-      const int32_t v = tid >= d ? scan[tid - d] : 0;
-      __syncthreads();
-      scan[tid] += v;
-      __syncthreads();
+    int32_t before = carry, all = 0;
+    for (int w = 0; w < SETUP_THREADS / 64; ++w) {
+      before += w < wave ? wave_sum[w] : 0;
+      all += wave_sum[w];
     }
     if (i < a.n_inst) {
-      const int32_t f = carry + scan[tid] - nb;
-      first_blk[i] = f;
+      const int32_t f = before + inc - nb;
+      if (once) first_blk[i] = f;
       if (in_lds) fb[i] = f;
-      if (nb > 0) atomicAdd(&n_active, 1);
     }
-    __syncthreads();
-    if (tid == SETUP_THREADS - 1) carry += scan[SETUP_THREADS - 1];
+    const int n = __popcll(__ballot(nb > 0));
+    if (lane == 0 && n > 0) atomicAdd(&n_active, n);
+    __syncthreads();  // wave_sum and carry are read
+    if (tid == 0) carry += all;
     __syncthreads();
   }
   const int32_t nblk = carry;
-  if (tid == 0) {
+  if (tid == 0 && in_lds) fb[a.n_inst] = nblk;
+  if (tid == 0 && once) {
     first_blk[a.n_inst] = nblk;
-    if (in_lds) fb[a.n_inst] = nblk;
     *wsp<int64_t>(a, a.L.nblk) = nblk;
     sync[SYNC_SOLVED] = 0;
     sync[SYNC_ABORT] = 0;
     sync[SYNC_EXITED] = 0;
     act_phase[0] = n_active;
   }
-  for (int p = tid + 1; p < MAXP + 2; p += SETUP_THREADS) act_phase[p] = 0;
-  for (int i = tid; i < a.n_inst; i += SETUP_THREADS) {
+  if (once)
+    for (int p = tid + 1; p < MAXP + 2; p += SETUP_THREADS) act_phase[p] = 0;
+  const int i0 = blockIdx.x * SETUP_THREADS + tid, stride = gridDim.x * SETUP_THREADS;
+  for (int i = i0; i < a.n_inst; i += stride) {
     inst_cnt[i] = 0;
     wsp<uint32_t>(a, a.L.inv)[i] = 0;
   }
@@ -396,8 +407,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void setup_kernel(StepArgs a) {
   // instance i owns batches fb[i] .. fb[i+1]-1: one wave per instance at a
   // time, its lanes over the instance's batches (stores only, no search)
   const int32_t* fbp = in_lds ? fb : first_blk;
-  const int lane = tid & 63;
-  for (int i = tid >> 6; i < a.n_inst; i += SETUP_THREADS / 64) {
+  for (int i = blockIdx.x * (SETUP_THREADS / 64) + wave; i < a.n_inst; i += gridDim.x * (SETUP_THREADS / 64)) {
     const int32_t f = fbp[i], nb = fbp[i + 1] - f;
     const int64_t base = in_lds ? lo_off[i] : a.offsets[i];
     for (int32_t k = lane; k < nb; k += 64) {
@@ -408,13 +418,13 @@ __global__ __launch_bounds__(SETUP_THREADS) void setup_kernel(StepArgs a) {
   }
   // state: the phase and flags words of every instance (the first solve
   // forms the rest)
-  for (int i = tid; i < a.n_inst; i += SETUP_THREADS) {
+  for (int i = i0; i < a.n_inst; i += stride) {
     const bool empty = fbp[i + 1] == fbp[i];
     uint64_t* words = reinterpret_cast<uint64_t*>(st + i);
     words[GN_W_PHASE] = gn_initial_word(GN_W_PHASE, nullptr, a.r, empty);
     words[GN_W_FLAGS] = gn_initial_word(GN_W_FLAGS, nullptr, a.r, empty);
   }
-  for (int i = tid; i < a.n_inst; i += SETUP_THREADS) {
+  for (int i = i0; i < a.n_inst; i += stride) {
     if (fbp[i + 1] != fbp[i]) continue;
     for (int k = 0; k < a.r; ++k) a.q_next[(int64_t)i * a.r + k] = a.q_n[(int64_t)i * a.r + k];
     crom_step_info inf;
@@ -423,6 +433,12 @@ __global__ __launch_bounds__(SETUP_THREADS) void setup_kernel(StepArgs a) {
     inf.obj_first = inf.obj_last = __builtin_nan("");
     a.info[i] = inf;
   }
+}
+
+// 512 instances (36 k batches): one workgroup 13 us, 32 workgroups 5.3.
+static dim3 setup_grid(int n_inst) {
+  constexpr int PER = SETUP_THREADS / 64;  // instances a workgroup fills at once
+  return dim3(n_inst > SETUP_LDS ? 1 : (unsigned)std::min(32, std::max(1, (n_inst + PER - 1) / PER)));
 }
 
 // Partial sums of one batch from J rows and residuals staged in LDS (jd
@@ -1748,8 +1764,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
         s_last = (old + 1 == nb);
       }
       __syncthreads();
-      const bool last = s_last != 0;
-      __syncthreads();  // every thread has read s_last before thread 0 may write it again
+      const bool last = s_last != 0;  // written again only after the next arrival's barrier
       if (p == 1 && w == blockIdx.x) trace_mark(a, 46);
       if (last) solve_instance<S::R, LAZY, NTH>(a, lds, inst, p, p == max_rounds);
       if (p == 1 && w == blockIdx.x) trace_mark(a, 47);
@@ -1907,7 +1922,7 @@ static crom_status launch_lls(StepArgs a, hipStream_t st) {
   auto k = rev ? lls_jets_kernel<S, NW, PREC, PF, WPE_REV, true> : lls_jets_kernel<S, NW, PREC, PF, WPE, false>;
   crom_status s = set_lds(k, lds_bytes);
   if (s != CROM_OK) return s;
-  hipLaunchKernelGGL(setup_kernel, dim3(1), dim3(SETUP_THREADS), 0, st, a);
+  hipLaunchKernelGGL(setup_kernel, setup_grid(a.n_inst), dim3(SETUP_THREADS), 0, st, a);
   if ((s = hip_check(hipGetLastError(), "setup launch")) != CROM_OK) return s;
   // up to 4,096 workgroups, each loading the parameters once for its
   // batches (one wave of resident workgroups measured the same: 1.080 vs
@@ -2085,7 +2100,7 @@ static crom_status launch_gn_rounds_t(StepArgs a, int max_rounds, hipStream_t st
   auto ks = gn_solve_kernel<S::R, NWS * 64>;
   crom_status s = set_lds(kr, lds_bytes);
   if (s != CROM_OK) return s;
-  hipLaunchKernelGGL(setup_kernel, dim3(1), dim3(SETUP_THREADS), 0, st, a);
+  hipLaunchKernelGGL(setup_kernel, setup_grid(a.n_inst), dim3(SETUP_THREADS), 0, st, a);
   if ((s = hip_check(hipGetLastError(), "setup launch")) != CROM_OK) return s;
   // one wave of resident workgroups (512 instances of the 2D decoder,
   // BF16: 10.66 -> 10.33 ms per step against up to 4,096 workgroups)
@@ -2223,7 +2238,7 @@ static crom_status launch_step_t(StepArgs a, int max_rounds, hipStream_t st) {
     resident = per_cu * ncu;
     resident_lds = lds_bytes;
   }
-  hipLaunchKernelGGL(setup_kernel, dim3(1), dim3(SETUP_THREADS), 0, st, a);
+  hipLaunchKernelGGL(setup_kernel, setup_grid(a.n_inst), dim3(SETUP_THREADS), 0, st, a);
   crom_status s = hip_check(hipGetLastError(), "setup launch");
   if (s != CROM_OK) return s;
   timer_mark(st);

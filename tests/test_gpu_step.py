@@ -402,3 +402,33 @@ def test_rounds_tail_matches_persistent(cuda, prec):
             for f in ("flags", "iters", "ls_evals", "obj_first", "obj_last"):
                 assert i1[f] == info[i][f], (scale, i, f)
     assert info["rounds"].max() > 6, info["rounds"]
+
+
+@pytest.mark.parametrize("n", [16, 17, 513, 2048, 2049])
+def test_many_instances_match_small_batches(cuda, n):
+    """The set-up of a batch, spread over workgroups (from 17 instances on, one
+    workgroup again above 2048): every instance, empty ones too, gets the bits
+    it gets in a batch of at most 16, which one workgroup sets up."""
+    import torch
+    from paper_2206_02607_amd import crom
+    g = np.random.default_rng(5)
+    wl = Heat1D(seed=3)
+    dec = crom.Decoder.from_layers(wl.layers, wl.m, precision="fp32", device=cuda)
+    counts = g.integers(3, 60, n)
+    counts[g.integers(0, n, 1 + n // 40)] = 0
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    y = torch.from_numpy(g.uniform(0.05, 0.95, (int(offsets[-1]), 1)).astype(np.float32)).to(cuda)
+    q0 = torch.from_numpy(g.uniform(-1, 1, (n, dec.r))).to(cuda)
+    nu = torch.from_numpy(g.uniform(0.1, 1.0, n)).to(cuda)
+    opts = crom.GNOptions(linearized=True)
+    st = crom.Stepper(dec, offsets, y)
+    q = st.step(q0, nu, 1e-5, opts)
+    flags = st.info()["flags"].copy()
+    for a in sorted({0, 16 * (n // 32), max(0, n - 13)}):
+        b = min(n, a + 16)
+        s1 = crom.Stepper(dec, offsets[a:b + 1] - offsets[a], y[int(offsets[a]):int(offsets[b])].contiguous())
+        q1 = s1.step(q0[a:b].contiguous(), nu[a:b].contiguous(), 1e-5, opts)
+        assert torch.equal(q1, q[a:b]), (a, b)
+        assert (s1.info()["flags"] == flags[a:b]).all()
+    empty = np.flatnonzero(counts == 0)
+    assert (flags[empty] & crom.FLAG_SINGULAR).all() and torch.equal(q[empty], q0[empty])
