@@ -452,8 +452,9 @@ constexpr int MSE_BLOCKS = 1024;
 // The shapes the fused pass is compiled for: its LDS holds one activation
 // tile per product and the registers its weight gradients, four at most.
 // It is the faster path at every size: forward and backward of 3 latents at
-// 4,999 points took 382 us layer by layer and takes 182, the gradients of
-// 16 snapshots of 16,384 points 0.92 ms and 0.33.
+// 4,999 points took 382 us layer by layer and takes 147 (with the forward's
+// latents in one launch), the gradients of 16 snapshots of 16,384 points 0.92
+// ms and 0.26.
 static bool fused_shape(const crom_net* n) {
   return n->width == TF_W && n->m == 2 && n->d == 1 && n->act == CROM_ACT_ELU && n->depth >= 3 && n->depth <= 5;
 }
