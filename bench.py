@@ -72,7 +72,7 @@ def source_hash() -> str:
     import hashlib
     h = hashlib.sha256()
     src = os.path.join(ROOT, "paper_2206_02607_amd", "csrc")
-    for name in ("common.hpp", "engine.hpp", "tune.hpp", "decode.hip", "step.hip", "../../include/crom.h"):
+    for name in ("common.hpp", "engine.hpp", "tune.hpp", "chain.hpp", "decode.hip", "step.hip", "../../include/crom.h"):
         path = os.path.normpath(os.path.join(src, name))
         with open(path, "rb") as f:
             h.update(os.path.basename(path).encode() + f.read())
