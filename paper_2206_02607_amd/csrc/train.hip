@@ -505,7 +505,7 @@ struct DecoderPass {
       carry = cv.take<f32x4>((size_t)wgs * 3 * TF_THREADS);
       a0 = cv.take<T>((size_t)wgs * FusedTile<T>::ROWS * FusedTile<T>::LD);
       cpart = cv.take<double>((size_t)items * 3 * W);
-      mpart = cv.take<double>((size_t)wgs * (2 * W + 2));
+      mpart = cv.take<double>((size_t)wgs * tf_out(depth - 1));
       csum = cv.take<double>((size_t)B * 3 * W);
       return;
     }
@@ -560,7 +560,7 @@ static crom_status fused_fwd_bwd(const crom_net* n, const float* x, int B, int64
   hipLaunchKernelGGL(k, dim3(wgs), dim3(TF_THREADS), sizeof(FusedLds<T, L>), st, a);
   FusedReduceArgs f{ws.part, ws.mpart, ws.cpart, wgs, L, a.chunks, pi, grad, dg_in ? nullptr : loss,
                     (double)((int64_t)B * P), ws.csum, B};
-  hipLaunchKernelGGL(fused_reduce_kernel, dim3(L * TF_MAT / 64 + (TF_W + 2 + 63) / 64 + B * (3 * TF_W / 64)),
+  hipLaunchKernelGGL(fused_reduce_kernel, dim3(L * TF_MAT / 64 + ((1 + L) * TF_W + 2 + 63) / 64 + B * (3 * TF_W / 64)),
                      dim3(TF_LANES * 64), 0, st, f);
   hipLaunchKernelGGL(layer1_grad_kernel, dim3((TF_W * (2 + r) + TF_W + B * r + 3) / 4), dim3(256), 0, st, ws.csum, q,
                      n->params + pi.w[0], B, TF_W, 2, r, grad + pi.w[0], grad + pi.b[0], dq);

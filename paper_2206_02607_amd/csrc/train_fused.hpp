@@ -19,7 +19,7 @@
 // fragments streaming through 32 registers from L2.  In a weight gradient
 // (K = rows; bfloat16 fragments by LDS transpose reads) it takes a 64 x 32
 // block of dW, 32 accumulators per layer; the bias gradient is a product with
-// ones.  LDS holds as many tiles of rows as there are products in one
+// ones, at most 32 rows in FP32 and FP64 from there.  LDS holds as many tiles of rows as there are products in one
 // direction: the last layer's activations stay in registers, dz_l takes the
 // place of a_l, and a_0, whose place dz_L takes (a fifth tile would not fit),
 // waits in memory and comes back while the upper layers' gradients are formed.
@@ -38,7 +38,9 @@ namespace crom {
 
 constexpr int TF_W = 128;
 constexpr int TF_THREADS = 512, TF_MAX_WG = 256;  // one workgroup per compute unit
-constexpr int TF_MAT = TF_W * TF_W + TF_W;        // a layer's partial gradient: dW, then db
+constexpr int TF_MAT = TF_W * TF_W;               // a layer's partial dW
+// a workgroup's FP64 partials: dWout (two halves of the rows), dbout, sum of squares, the layers' db
+constexpr int tf_out(int L) { return (2 + L) * TF_W + 2; }
 
 // Rows of a block (the LDS holds a tile of them per product), the LDS row
 // (padded: 8 or 4 banks further on than the one before), K of one 16-byte
@@ -71,7 +73,7 @@ struct FusedArgs {
   f32x4* carry;               // [workgroups][3][TF_THREADS]: a chunk's sums of dz_0 between its blocks
   void* a0;                   // [workgroups][ROWS][LD]: a_0 of the block, as it lies in LDS
   double* spart;              // [items][3][W]: sums of dz_0, dz_0 x_0, dz_0 x_1
-  double* opart;              // [workgroups][2 W + 2]: dWout (two halves of the rows), dbout, sum of squares
+  double* opart;              // [workgroups][tf_out(layers)]
 };
 
 // Weight fragments of every hidden-to-hidden layer (forward and transposed; the rows of a pair of M-tiles are dealt so that a lane ends
@@ -104,9 +106,13 @@ __global__ __launch_bounds__(256) void fused_prep_kernel(const float* __restrict
 }
 
 // Sum over the 16 lanes of a DPP row, in every lane (rotations by 8, 4, 2, 1).
-__device__ __forceinline__ float row16_sum(float v) {
-  auto rot = [](float x, auto ctrl) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, false));
+__device__ __forceinline__ double row16_sum(double v) {
+  auto rot = [](double x, auto ctrl) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, decltype(ctrl)::value, 0xf, 0xf, false);
+    const unsigned hi =
+        (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), decltype(ctrl)::value, 0xf, 0xf, false);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
   };
   v += rot(v, std::integral_constant<int, 0x128>{});
   v += rot(v, std::integral_constant<int, 0x124>{});
@@ -122,6 +128,7 @@ struct FusedLds {
   float wx[2][TF_W], c[TF_W], bias[L][TF_W], wo[TF_W], xs[2][ROWS];
   float dg[ROWS];             // the block's snapshot values (or cotangents), then dL/dg
   double dwo[2][TF_W];        // dWout, two halves of the rows
+  double db[L][TF_W];
   double loss[ROWS][2];       // per row of a block: sums of dL/dg and of the squared errors
 };
 
@@ -149,16 +156,15 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
 
   if (tid < ROWS) s.loss[tid][0] = s.loss[tid][1] = 0.0;
   if (tid < 2 * TF_W) (&s.dwo[0][0])[tid] = 0.0;
+  if (tid < L * TF_W) (&s.db[0][0])[tid] = 0.0;
 
-  f32x4 dw[L][4][2], db[L];
+  f32x4 dw[L][4][2];
 #pragma unroll
-  for (int l = 0; l < L; ++l) {
-    db[l] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int l = 0; l < L; ++l)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) dw[l][i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  }
 
   // Tile `slot` of the activations, its offset formed where it is used: the
   // compiler would otherwise keep every slot's per-lane addresses in
@@ -243,8 +249,13 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       return 1.0f;
     }
   };
-  // dw += dz^T a over the block's rows, db += dz^T 1 (one of this wave's M-tiles)
-  auto weight_grad = [&](const T* Z, const T* Y, f32x4 (&d)[4][2], f32x4& b) {
+  // dw += dz^T a over the block's rows, db += dz^T 1 (one of this wave's
+  // M-tiles): products with ones over 32 rows (FP32: 16), FP64 from there
+  auto weight_grad = [&](const T* Z, const T* Y, f32x4 (&d)[4][2], double* db) {
+    constexpr int GROUP = F::BF ? 1 : 4;
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 b = zero;
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
     for (int kk = 0; kk < ROWS / KR; ++kk) {
       decltype(ones()) y[2];
@@ -257,6 +268,15 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         for (int j = 0; j < 2; ++j) d[i][j] = mfma(z, y[j], d[i][j]);
       }
       b = mfma(columns(Z, kk, mq + 16 * (wave & 3)), ones(), b);
+      if (kk % GROUP == GROUP - 1) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) t[v] += (double)b[v];
+        b = zero;
+      }
+    }
+    if (lr == 0) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) db[mq + 16 * (wave & 3) + 4 * lg + v] += t[v];
     }
   };
   // the thread's index, opaque: the addresses formed from it are computed in
@@ -418,8 +438,8 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          dwo[e] = row16_sum(dwo[e]);
-          if ((me & 15) == 0) s.dwo[half][u0 + e] += (double)dwo[e];
+          const double t = row16_sum((double)dwo[e]);
+          if ((me & 15) == 0) s.dwo[half][u0 + e] += t;
         }
       }
       __syncthreads();
@@ -439,7 +459,7 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[n][e] = (T)(acc[e >> 2][n][e & 3] * elu_d1_from_a((float)gv[e]));
         }
-        weight_grad(Z, G, dw[l - 1], db[l - 1]);
+        weight_grad(Z, G, dw[l - 1], s.db[l - 1]);
         __syncthreads();  // dz_l and a_{l-1} have been read
         if (l == L) reload_a0();  // where dz_L was
 #pragma unroll
@@ -514,13 +534,10 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int v = 0; v < 4; ++v) d[(mq + 16 * i + 4 * lg + v) * TF_W + nq + 16 * j + lr] = dw[l][i][j][v];
-    if (lr == 0) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) d[TF_W * TF_W + mq + 16 * (wave & 3) + 4 * lg + v] = db[l][v];
-    }
   }
-  double* op = a.opart + (size_t)blockIdx.x * (2 * TF_W + 2);
+  double* op = a.opart + (size_t)blockIdx.x * tf_out(L);
   if (tid < 2 * TF_W) op[tid] = (&s.dwo[0][0])[tid];
+  if (tid < L * TF_W) op[2 * TF_W + 2 + tid] = (&s.db[0][0])[tid];
   if (wave == 0) {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
@@ -534,8 +551,8 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
 
 // Sums the workgroups' partials in order (16 interleaved lanes per output,
 // then the lanes; four lanes kept too few loads in flight: 28 us for the 67 MB
-// of 256 workgroups): blocks [0, nb_w) the layers' dW and db, then dWout, dbout
-// and the loss, then S[seg][3][W] from the chunks.
+// of 256 workgroups): blocks [0, nb_w) the layers' dW, then dWout, dbout, the
+// loss and the layers' db, then S[seg][3][W] from the chunks.
 struct FusedReduceArgs {
   const float* part;
   const double *opart, *spart;
@@ -557,7 +574,7 @@ __global__ __launch_bounds__(TF_LANES * 64) void fused_reduce_kernel(FusedReduce
     for (int l = 1; l < TF_LANES; ++l) s += v[64 * l + t];
     return s;
   };
-  const int nb_w = a.L * TF_MAT / 64, nb_o = (TF_W + 2 + 63) / 64;
+  const int nb_w = a.L * TF_MAT / 64, n_o = (1 + a.L) * TF_W + 2, nb_o = (n_o + 63) / 64;
   const int blk = blockIdx.x;
   if (blk < nb_w) {  // FP32 partials, summed in FP32
     float* shf = reinterpret_cast<float*>(sh);
@@ -569,25 +586,25 @@ __global__ __launch_bounds__(TF_LANES * 64) void fused_reduce_kernel(FusedReduce
     shf[lane * 64 + t] = s;
     __syncthreads();
     if (threadIdx.x < 64)
-      a.grad[(i < TF_W * TF_W ? a.pi.w[1 + l] + i : a.pi.b[1 + l] + i - TF_W * TF_W)] =
-          total(shf);
+      a.grad[a.pi.w[1 + l] + i] = total(shf);
     return;
   }
   double s = 0.0;
   if (blk < nb_w + nb_o) {
     const int o = (blk - nb_w) * 64 + t;
-    if (o < TF_W + 2) {
+    if (o < n_o) {
       for (int z = lane; z < a.wgs; z += TF_LANES) {
-        const double* p = a.opart + (size_t)z * (2 * TF_W + 2);
+        const double* p = a.opart + (size_t)z * tf_out(a.L);
         s += o < TF_W ? p[o] + p[TF_W + o] : p[TF_W + o];
       }
     }
     sh[lane][t] = s;
     __syncthreads();
-    if (threadIdx.x < 64 && o < TF_W + 2) {
+    if (threadIdx.x < 64 && o < n_o) {
       s = total(&sh[0][0]);
       if (o < TF_W) a.grad[a.pi.w[a.L + 1] + o] = (float)s;
       else if (o == TF_W) a.grad[a.pi.b[a.L + 1]] = (float)s;
+      else if (o > TF_W + 1) a.grad[a.pi.b[1 + (o - TF_W - 2) / TF_W] + (o - TF_W - 2) % TF_W] = (float)s;
       else if (a.loss) *a.loss = (float)(s / a.n);
     }
     return;

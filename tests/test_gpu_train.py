@@ -538,3 +538,31 @@ def test_fused_pass_edges(cuda, depth, r, B, P):
     errs["vjp"] = normwise_rel(gp.cpu().numpy(), gd.cpu().numpy())
     bad = {k: v for k, v in errs.items() if not v <= TOL["bf16"]}
     assert not bad, bad
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("depth", [3, 5])
+def test_bias_gradient_sums_in_64_bits(cuda, depth, prec):
+    """Bias and output-weight gradients are sums over all rows: FP32 over at
+    most 32 rows, FP64 from there.  The net passes the cotangent down unchanged
+    (identity weights, every activation 1), and the cotangents are 2^20, of
+    either sign by snapshot, with ones 2^-19 of them in between: 32 rows fit
+    the 24 bits of FP32, more do not, and the large ones cancel.  So the sums
+    are whole numbers and come out exactly."""
+    import torch
+    from paper_2206_02607_amd import crom
+    B, P, W, r = 16, 16384, 128, 8
+    ones = np.ones(W)
+    layers = [(np.zeros((W, 2 + r)), ones)] + [(np.eye(W), 0 * ones)] * (depth - 1) + [(0.5 * ones[None], np.zeros(1))]
+    mask = rng(7).uniform(size=(B // 2, P)) < 0.25
+    dg = np.concatenate([np.where(mask, 2.0, 2.0**20), np.where(mask, 2.0, -(2.0**20))])
+    D = crom.Decoder.from_layers([(w.astype(np.float32), b.astype(np.float32)) for w, b in layers], 2, precision=prec,
+                                 device=cuda)
+    gp, _ = crom.decode_vjp(D, torch.zeros(P, 2, device=cuda), torch.zeros(B, r, device=cuda),
+                            torch.from_numpy(dg.astype(np.float32)).to(cuda).reshape(B, P, 1))
+    got = _split(gp.cpu().numpy(), layers)
+    total = dg.sum()  # exact in FP64
+    np.testing.assert_array_equal(got[-1][0], np.full((1, W), total, np.float32))
+    np.testing.assert_array_equal(got[-1][1], np.full(1, total, np.float32))
+    for l in range(depth):
+        np.testing.assert_array_equal(got[l][1], np.full(W, total / 2, np.float32), err_msg=f"layer {l}")
