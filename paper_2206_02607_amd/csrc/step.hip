@@ -182,7 +182,7 @@ __device__ __forceinline__ uint64_t gn_initial_word(int w, const double* q_n, in
 
 struct WsLayout {
   size_t blk_start, blk_inst, first_blk, nblk, sync, act_phase, inst_cnt, inv, targets, rho0, partials,
-      state, jets, work, work_cnt, jbuf, bcnt, total;
+      state, jets, work, jbuf, bcnt, total;
   int64_t nblk_max;
   int nred;
   int nj;  // FP32 values per sample in the jets buffer (0: none)
@@ -225,7 +225,6 @@ static WsLayout ws_layout(int r, int d, int m, int n_inst, int64_t total) {
   L.state = o;     o = align256(o + sizeof(GNState) * (size_t)n_inst);
   L.jets = o;      o = align256(o + 4 * (size_t)total * L.nj);
   L.work = o;      o = align256(o + 4 * 2 * (size_t)L.nblk_max);  // round kernels: two batch lists
-  L.work_cnt = o;  o = align256(o + 8 * (size_t)(MAXP + 2));  // each round's length
   // elastic step: each batch's Jacobian rows and residuals, assembled from
   // the workgroups of its latent-tangent chunks, and their arrival counts
   const size_t jrows = L.nj ? (size_t)PT * d * (r + TV) : 0;
@@ -1306,6 +1305,19 @@ __device__ __forceinline__ CholOut chol_solve(const double* up, const double* b)
   else return row_chol_solve<R>(up, b);
 }
 
+// A value every lane holds, in scalar registers (read from LDS or by ld_c it
+// would make the loops it bounds divergent ones, at 10 to 25 registers).
+__device__ __forceinline__ uint64_t uniform(uint64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// A round's word in act_phase: the active instances and, above them, the
+// batches in its work list (round kernels).
+__device__ __forceinline__ int64_t round_active(uint64_t w) { return (int64_t)(w & 0xffffffffu); }
+__device__ __forceinline__ int64_t round_batches(uint64_t w) { return (int64_t)(w >> 32); }
+
 // The same as a call: its registers then do not add to the caller's (the
 // round kernels, whose evaluations leave none).
 template <int R>
@@ -1329,7 +1341,8 @@ __device__ __attribute__((noinline)) CholOut chol_solve_call(const double* up, c
 // NTH: the thread count whose summation order the partials take (0: the
 // workgroup's own), so that workgroups of different sizes agree bit for bit.
 // LIST: an instance that goes on appends its batches to the next round's
-// work list (in any order: each batch keeps its own partials slot).
+// work list (in any order: each batch keeps its own partials slot), whose
+// length is the upper half of the round's word in act_phase.
 template <int R, bool LAZY = false, int NTH = 0, bool LIST = false>
 __device__ void solve_instance(const StepArgs& a, char* lds, int inst, int p, bool is_last) {
   constexpr int NA = R * (R + 1) / 2;
@@ -1572,13 +1585,14 @@ __device__ void solve_instance(const StepArgs& a, char* lds, int inst, int p, bo
     st_c(reinterpret_cast<uint64_t*>(gst) + w, reinterpret_cast<const uint64_t*>(st)[w]);
   if (threadIdx.x == 0) {
     st_c(wsp<uint32_t>(a, a.L.inst_cnt) + inst, 0u);
-    if (!s_done) atomicAdd(reinterpret_cast<unsigned long long*>(wsp<int64_t>(a, a.L.act_phase) + p + 1), 1ull);
+    if (!LIST && !s_done) atomicAdd(wsp<unsigned long long>(a, a.L.act_phase) + p + 1, 1ull);
   }
   if constexpr (LIST) {
     if (s_done == 0) {  // uniform
       __shared__ int64_t s_base;
       if (threadIdx.x == 0)
-        s_base = (int64_t)atomicAdd(wsp<unsigned long long>(a, a.L.work_cnt) + p + 1, (unsigned long long)(b1 - b0));
+        s_base = round_batches(atomicAdd(wsp<unsigned long long>(a, a.L.act_phase) + p + 1,
+                                         ((unsigned long long)(b1 - b0) << 32) + 1));
       __syncthreads();
       int32_t* next = wsp<int32_t>(a, a.L.work) + (int64_t)((p + 1) % 2) * a.L.nblk_max + s_base;
       for (int32_t i = threadIdx.x; i < b1 - b0; i += nth) st_c(next + i, b0 + i);
@@ -1957,14 +1971,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
   __shared__ int s_ph, s_lt;
   __shared__ double qdl[TV * RMAX];
   // Round p >= 1 evaluates the batches that the solves of round p - 1 listed
-  // for their continuing instances (list p % 2, a count per round); this
-  // round's solves fill the other list.  Round 0 evaluates every batch and
-  // clears the counts (its solves run after this kernel on the same stream).
-  int64_t* work_cnt = wsp<int64_t>(a, a.L.work_cnt);
-  if (p == 0 && blockIdx.x == 0)
-    for (int i = threadIdx.x; i < MAXP + 2; i += NW * 64) work_cnt[i] = 0;
-  if (ld_c(wsp<int64_t>(a, a.L.act_phase) + p) == 0) return;  // uniform: nothing active in this round
-  const int64_t nblk = p == 0 ? *wsp<int64_t>(a, a.L.nblk) : work_cnt[p];
+  // for their continuing instances (list p % 2); this round's solves fill the
+  // other list.  Round 0 evaluates every batch.
+  const uint64_t active = uniform(ld_c(wsp<uint64_t>(a, a.L.act_phase) + p));
+  if (active == 0) return;  // uniform: nothing active in this round
+  const int64_t nblk = p == 0 ? *wsp<int64_t>(a, a.L.nblk) : round_batches(active);
   if ((int64_t)blockIdx.x >= nblk) return;
   const int32_t* list = wsp<int32_t>(a, a.L.work) + (int64_t)(p % 2) * a.L.nblk_max;
   float* par = reinterpret_cast<float*>(lds + T::PAR);
@@ -2028,9 +2039,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1))) vo
   using T = StepTraits<S, NW, PREC, PF, PK_HEAT, true>;
   extern __shared__ __align__(16) char lds[];
   __shared__ int s_ph, s_lt, s_last, s_abort;
-  __shared__ int64_t s_act, s_n;
+  __shared__ uint64_t s_act;
   __shared__ double qdl[TV * RMAX];
-  const int64_t* act_phase = wsp<int64_t>(a, a.L.act_phase);
+  const uint64_t* act_phase = wsp<uint64_t>(a, a.L.act_phase);
   if (ld_c(act_phase + p0) == 0) return;  // uniform over the grid: nothing active
   float* par = reinterpret_cast<float*>(lds + T::PAR);
   T::E0::PC::load(par, a.params, a.pi, a.depth, NW * 64);
@@ -2039,17 +2050,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1))) vo
   const int32_t* first_blk = wsp<int32_t>(a, a.L.first_blk);
   const GNState* state = wsp<GNState>(a, a.L.state);
   uint64_t target = 0;  // solves of the rounds before, once they are all counted
-  for (int p = 0; p < p0; ++p) target += (uint64_t)ld_c(act_phase + p);
+  for (int p = 0; p < p0; ++p) target += (uint64_t)round_active(ld_c(act_phase + p));
   for (int p = p0; p <= max_rounds; ++p) {
-    if (threadIdx.x == 0) {  // final: written by round p - 1's solves
-      s_act = ld_c(act_phase + p);
-      s_n = ld_c(wsp<int64_t>(a, a.L.work_cnt) + p);
-    }
+    if (threadIdx.x == 0) s_act = ld_c(act_phase + p);  // final: written by round p - 1's solves
     __syncthreads();
-    const int64_t act = s_act, n = s_n;
+    const uint64_t act = uniform(s_act);
     __syncthreads();
     if (act == 0) break;
-    target += (uint64_t)act;
+    target += (uint64_t)round_active(act);
+    const int64_t n = round_batches(act);
     const int32_t* list = wsp<int32_t>(a, a.L.work) + (int64_t)(p % 2) * a.L.nblk_max;
     for (int64_t it = blockIdx.x; it < n; it += gridDim.x) {
       const int64_t blk = (int64_t)ld_c(list + it);

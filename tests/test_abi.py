@@ -208,3 +208,13 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(crom, "_lib", None)
     with pytest.raises(crom.CromError):
         crom.lib()
+
+
+@pytest.mark.parametrize("shape,samples", [(dict(m=1, r=3, d=1, width=32), 3_015_871), (dict(), 1_688_127)])
+def test_step_workspace_at_the_static_limit(shape, samples):
+    """The largest single instances that the static workspace has taken: their
+    layout fills its 64 MiB, so one that grows refuses them."""
+    L = crom.lib()
+    n = ctypes.c_size_t(0)
+    assert L.crom_step_workspace(ctypes.byref(_net(**shape)), 1, samples, ctypes.byref(n)) == 0
+    assert n.value <= L.crom_step_static_capacity() == 64 << 20
