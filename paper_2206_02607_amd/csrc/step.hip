@@ -33,7 +33,8 @@
 // tetrahedra (fe_prepare); the inversion is the same.  An optional initial
 // guess per instance costs one round (PH_GUESS) and becomes the start when
 // its objective is lower.  Large batches run the same phases as round
-// kernels (one evaluation launch and one solve launch per round).
+// kernels (one evaluation launch and one solve launch per round; the last
+// rounds share one launch).
 // The residual is the paper's f_{n+1} - g(q) written incrementally: over a
 // time step g moves by a small fraction of its size, and a difference
 // carried through the network keeps its rounding error relative to itself,
@@ -182,7 +183,7 @@ __device__ __forceinline__ uint64_t gn_initial_word(int w, const double* q_n, in
 
 struct WsLayout {
   size_t blk_start, blk_inst, first_blk, nblk, sync, act_phase, inst_cnt, inv, targets, rho0, partials,
-      state, jets, work, jbuf, bcnt, total;
+      state, jets, work, tickets, jbuf, bcnt, total;
   int64_t nblk_max;
   int nred;
   int nj;  // FP32 values per sample in the jets buffer (0: none)
@@ -225,6 +226,7 @@ static WsLayout ws_layout(int r, int d, int m, int n_inst, int64_t total) {
   L.state = o;     o = align256(o + sizeof(GNState) * (size_t)n_inst);
   L.jets = o;      o = align256(o + 4 * (size_t)total * L.nj);
   L.work = o;      o = align256(o + 4 * 2 * (size_t)L.nblk_max);  // round kernels: two batch lists
+  L.tickets = o;   o = align256(o + 8);
   // elastic step: each batch's Jacobian rows and residuals, assembled from
   // the workgroups of its latent-tangent chunks, and their arrival counts
   const size_t jrows = L.nj ? (size_t)PT * d * (r + TV) : 0;
@@ -393,6 +395,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void setup_kernel(StepArgs a) {
     sync[SYNC_SOLVED] = 0;
     sync[SYNC_ABORT] = 0;
     sync[SYNC_EXITED] = 0;
+    *wsp<uint64_t>(a, a.L.tickets) = 0;
     act_phase[0] = n_active;
   }
   if (once)
@@ -2027,21 +2030,27 @@ __global__ __launch_bounds__(NTH) void gn_solve_kernel(StepArgs a, int p, int is
 // a pair of empty launches takes some 6 us all the same (FP32 step of 64
 // untrained instances at 1,100 samples on average: 13 rounds with work, 62
 // launched).  Here the workgroup that completes an instance's last batch of a
-// round solves the instance at once, and the grid (no more workgroups than
-// the device holds at once) waits for the solves, as in the persistent
-// kernel, and goes on until nothing is active.  Only for the last rounds: the
+// round solves the instance at once, and the grid goes on when the round's
+// solves are counted, until nothing is active.  Only for the last rounds: the
 // arrival costs every batch about 2 us, which few batches on an idle device
 // do not notice (all rounds this way: 5.3 -> 7.0 ms for 256 instances in
 // BF16).  Same evaluations and solves as the rounds of their own.
+//
+// Batches go to workgroups by tickets, numbered through all rounds: a running
+// workgroup draws one, evaluates that batch and draws the next; one that lies
+// beyond the round is kept for the following rounds.  So every batch is in a
+// running workgroup's hands, and no wait depends on workgroups that are not
+// placed yet: another stream's kernels may hold any part of the device.
 template <class S, int NW, int PREC, int PF, int NTH>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1))) void gn_tail_kernel(StepArgs a, int p0,
                                                                                              int max_rounds) {
   using T = StepTraits<S, NW, PREC, PF, PK_HEAT, true>;
   extern __shared__ __align__(16) char lds[];
   __shared__ int s_ph, s_lt, s_last, s_abort;
-  __shared__ uint64_t s_act;
+  __shared__ uint64_t s_act, s_ticket;
   __shared__ double qdl[TV * RMAX];
   const uint64_t* act_phase = wsp<uint64_t>(a, a.L.act_phase);
+  unsigned long long* tickets = wsp<unsigned long long>(a, a.L.tickets);
   if (ld_c(act_phase + p0) == 0) return;  // uniform over the grid: nothing active
   float* par = reinterpret_cast<float*>(lds + T::PAR);
   T::E0::PC::load(par, a.params, a.pi, a.depth, NW * 64);
@@ -2051,17 +2060,20 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1))) vo
   const GNState* state = wsp<GNState>(a, a.L.state);
   uint64_t target = 0;  // solves of the rounds before, once they are all counted
   for (int p = 0; p < p0; ++p) target += (uint64_t)round_active(ld_c(act_phase + p));
+  if (threadIdx.x == 0) s_ticket = atomicAdd(tickets, 1ull);
+  int64_t first = 0;  // the round's first ticket
   for (int p = p0; p <= max_rounds; ++p) {
     if (threadIdx.x == 0) s_act = ld_c(act_phase + p);  // final: written by round p - 1's solves
     __syncthreads();
     const uint64_t act = uniform(s_act);
+    int64_t ticket = (int64_t)uniform(s_ticket);
     __syncthreads();
     if (act == 0) break;
     target += (uint64_t)round_active(act);
-    const int64_t n = round_batches(act);
+    const int64_t end = first + round_batches(act);
     const int32_t* list = wsp<int32_t>(a, a.L.work) + (int64_t)(p % 2) * a.L.nblk_max;
-    for (int64_t it = blockIdx.x; it < n; it += gridDim.x) {
-      const int64_t blk = (int64_t)ld_c(list + it);
+    while (ticket < end) {
+      const int64_t blk = (int64_t)ld_c(list + (ticket - first));
       const int inst = blk_inst[blk];
       if (threadIdx.x == 0) {
         s_ph = ld_c(&state[inst].phase);
@@ -2070,6 +2082,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1))) vo
       __syncthreads();
       const int ph = s_ph, lt = s_lt;
       __syncthreads();
+      if (threadIdx.x == 0) s_ticket = atomicAdd(tickets, 1ull);  // arrives during the evaluation
       if (ph == PH_TRIALS && lt > 0)
         eval_trials_batch<S, NW, PREC, PF, false>(a, lds, par, qdl, blk, inst, -1, false);
       else
@@ -2082,15 +2095,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1))) vo
                  (uint32_t)(first_blk[inst + 1] - first_blk[inst]);
       __syncthreads();
       const bool last = s_last != 0;
-      __syncthreads();  // every thread has read s_last before thread 0 may write it again
+      ticket = (int64_t)uniform(s_ticket);
+      __syncthreads();  // every thread has read them before thread 0 may write them again
       if (last) solve_instance<S::R, true, NTH, true>(a, lds, inst, p, p == max_rounds);
     }
+    first = end;
     if (threadIdx.x == 0) s_abort = wait_solved(wsp<uint64_t>(a, a.L.sync), target);
     __syncthreads();
     if (s_abort != 0) break;
   }
   leave_rounds(a);
 }
+
+constexpr int64_t TAIL_MAX_WG = 256;  // compute units
 
 // NWS: the waves of the persistent kernel whose solve the rounds repeat (its
 // thread count fixes the solve's summation order), independent of the
@@ -2118,13 +2135,22 @@ static crom_status launch_gn_rounds_t(StepArgs a, int max_rounds, hipStream_t st
   if ((s = resident_grid(rc, reinterpret_cast<const void*>(kr), NW * 64, lds_bytes, &g)) != CROM_OK) return s;
   if (g > a.L.nblk_max) g = a.L.nblk_max;
   if (g < 1) g = 1;
-  // launches of their own: two rounds per iteration (a trial, now and then a
-  // shorter one), more of them the larger the batch, whose late rounds still
-  // fill the device; then the tail.  FP32 step of 64 untrained instances
-  // (4.5 k batches) 1.62 -> 1.42 ms, BF16 1.73 -> 1.63; 256 instances (18 k)
-  // with the tail after two rounds per iteration 5.30 -> 5.46 (BF16)
+  // Launches of their own: the first rounds, which fill the device, more of
+  // them the larger the batch; then the tail, whose one workgroup per compute
+  // unit is slower while a round has many batches.  How long that is depends
+  // on the precision: the coarser the operands, the more instances go on
+  // backtracking (on average 3 to 5 rounds per instance in FP32, 7 to 16 in
+  // BF16, 15 to 24 in BF16_PURE).  Rounds per iteration before the tail
+  // against all rounds in launches of their own, us, untrained decoders, 64
+  // instances of 1,100 samples: 2D FP32 2: 2,020, all: 2,150; 2D BF16 2: 1,740,
+  // all: 1,800; 1D BF16 2: 830, 3: 670, all: 750; BF16_PURE 1D 2: 1,200, 4: 820,
+  // all: 890, r = 16 4: 3,590, 6: 3,380, all: 3,460.  r = 16 in BF16, 2,000
+  // instances of 16 samples: 2: 3,770, 4: 3,360, all: 3,330.
+  constexpr int PER_ITER = PREC == PREC_BF16_PURE ? (S::R > 8 ? 6 : 4)
+                           : PREC == PREC_BF16    ? (S::R > 8 ? 4 : S::W < 128 ? 3 : 2)
+                                                  : 2;
   const int64_t share = std::max<int64_t>(1, a.L.nblk_max / 4096);
-  const int own = REV ? (int)std::min<int64_t>(max_rounds, 2 * share * a.max_iter) : max_rounds;
+  const int own = REV ? (int)std::min<int64_t>(max_rounds, PER_ITER * share * a.max_iter) : max_rounds;
   timer_mark(st);
   for (int p = 0; p <= own; ++p) {
     hipLaunchKernelGGL(kr, dim3((unsigned)g), dim3(NW * 64), lds_bytes, st, a, p);
@@ -2136,10 +2162,13 @@ static crom_status launch_gn_rounds_t(StepArgs a, int max_rounds, hipStream_t st
       static_assert(SOLVE_LDS <= T::PAR, "solve scratch fits below the parameter cache");
       auto kt = gn_tail_kernel<S, NW, PREC, PF, NWS * 64>;
       if ((s = set_lds(kt, lds_bytes)) != CROM_OK) return s;
+      // one workgroup per compute unit: with more, tickets drawn together land
+      // on one unit (1D FP32, 64 instances of 1,100 samples, three per SIMD:
+      // 540 us, one per unit 500)
       static ResidentCache rct;
       int64_t gt = 0;
       if ((s = resident_grid(rct, reinterpret_cast<const void*>(kt), NW * 64, lds_bytes, &gt)) != CROM_OK) return s;
-      gt = std::max<int64_t>(1, std::min(gt, a.L.nblk_max));
+      gt = std::max<int64_t>(1, std::min<int64_t>({gt, TAIL_MAX_WG, a.L.nblk_max}));
       hipLaunchKernelGGL(kt, dim3((unsigned)gt), dim3(NW * 64), lds_bytes, st, a, own + 1, max_rounds);
     }
   }
@@ -2307,8 +2336,7 @@ static crom_status step_prec(int prec, const StepArgs& a, int rounds, hipStream_
       return launch_gn_rounds<S, NWL, PREC_BF16, CROM_LIN_PF, CROM_LIN_WPE, CROM_GN_REV_WPE, NWB>(a, rounds, st);
     if constexpr (ALL) {
       if (prec == CROM_PREC_BF16_PURE)
-        return launch_gn_rounds<S, NWL, PREC_BF16_PURE, CROM_LIN_PF, CROM_LIN_WPE, CROM_GN_REV_WPE, NWB>(a, rounds,
-                                                                                                     st);
+        return launch_gn_rounds<S, NWL, PREC_BF16_PURE, CROM_LIN_PF, CROM_LIN_WPE, (S::R <= 8 ? 3 : 2), NWB>(a, rounds, st);
       return launch_gn_rounds<S, NWF, PREC_BF16X3, 0, 1, 1, NWF>(a, rounds, st);
     }
     return fail(CROM_ERR_UNSUPPORTED, "precision");

@@ -432,3 +432,35 @@ def test_many_instances_match_small_batches(cuda, n):
         assert (s1.info()["flags"] == flags[a:b]).all()
     empty = np.flatnonzero(counts == 0)
     assert (flags[empty] & crom.FLAG_SINGULAR).all() and torch.equal(q[empty], q0[empty])
+
+
+@pytest.mark.parametrize("prec,max_iter,launched", [("fp32", 2, 4), ("bf16", 2, 4), ("bf16pure", 1, 4)])
+def test_large_batches_on_two_streams(cuda, prec, max_iter, launched):
+    """Steps of more than 1,024 batches share the device: two of them at once,
+    each with more rounds than are launched one by one, finish
+    with the bits they have alone, and neither gives up waiting."""
+    import torch
+    from paper_2206_02607_amd import crom
+    opts = crom.GNOptions(max_iter=max_iter, tol_step=1e-12, armijo_c=0.49, ls_shrink=0.9, ls_max=30)
+    runs = []
+    for seed in (11, 12):
+        wb = Batched2D(seed=seed, n_inst=24, s_min=700, s_max=900)
+        dec = crom.Decoder.from_layers(wb.layers, wb.m, precision=prec, device=cuda)
+        st = crom.Stepper(dec, wb.offsets, torch.from_numpy(wb.samples).to(cuda))
+        q0, nu = torch.from_numpy(wb.q0).to(cuda), torch.from_numpy(wb.mu).to(cuda)
+        alone = st.step(q0, nu, 0.05, opts).clone()
+        info = st.info().copy()
+        assert info["rounds"].max() > launched and not (info["flags"] & crom.FLAG_ABORTED).any()
+        runs.append((st, q0, nu, alone, info, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for k in range(8):
+        got = []
+        for st, q0, nu, alone, info, stream in runs:
+            with torch.cuda.stream(stream):
+                got.append(st.step(q0, nu, 0.05, opts))
+        torch.cuda.synchronize()
+        for q, (st, q0, nu, alone, info, stream) in zip(got, runs):
+            assert torch.equal(q, alone), k
+            now = st.info()
+            for f in ("flags", "iters", "ls_evals", "obj_first", "obj_last", "rounds"):
+                np.testing.assert_array_equal(now[f], info[f], err_msg=f)
