@@ -6,7 +6,8 @@
 //
 // Grids are batched: `n_grid` independent fields of the same shape, one
 // after another.  1D fields take one launch per substep; 2D fields advance
-// many substeps per launch in registers.
+// many substeps per launch in registers, except many small or narrow fields
+// and single substeps, which take one launch each too.
 #include "common.hpp"
 
 // Evaluate exactly in the written order (no fused multiply-add), so that the
@@ -38,7 +39,27 @@ __global__ void fd1d_kernel(const double* __restrict__ u, double* __restrict__ v
   }
 }
 
-// 2D fields [n_grid][nx][ny] (index [i_x][i_y]), `sub` substeps per launch.
+// One substep on a batch of 2D fields [n_grid][nx][ny] (index [i_x][i_y]).
+__global__ void fd2d_step_kernel(const double* __restrict__ u, double* __restrict__ v, const double* __restrict__ nu,
+                                 int nu_per_node, int64_t nx, int64_t ny, int64_t n_grid, double dt, double dx2) {
+  const int64_t plane = nx * ny, total = plane * n_grid;
+  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < total; k += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t gidx = k / plane, r = k - gidx * plane;
+    const int64_t i = r / ny, j = r - i * ny;
+    double out = 0.0;
+    if (i > 0 && i < nx - 1 && j > 0 && j < ny - 1) {
+      const double c = u[k];
+      const double xm = i - 1 > 0 ? u[k - ny] : 0.0, xp = i + 1 < nx - 1 ? u[k + ny] : 0.0;
+      const double ym = j - 1 > 0 ? u[k - 1] : 0.0, yp = j + 1 < ny - 1 ? u[k + 1] : 0.0;
+      const double lap = ((((xm + xp) + ym) + yp) - 4.0 * c) / dx2;
+      const double nv = nu_per_node ? nu[k] : nu[gidx];
+      out = c + (dt * nv) * lap;
+    }
+    v[k] = out;
+  }
+}
+
+// 2D fields, `sub` substeps per launch.
 //
 // A launch per substep was bound by the launch, not by memory: 40 fields of
 // 128 x 128 (10 MB read and written) took 6.3 us a substep, where the copy
@@ -243,35 +264,50 @@ static int64_t fd_tiles(int64_t n, int T, int halo) {
   return n <= T ? 1 : (n - T + (T - 2 * halo) - 1) / (T - 2 * halo) + 1;
 }
 
-static crom_status fd2d_run(int64_t nx, int64_t ny, int64_t n_grid, const double* nu, int nu_per_node, double dx2,
-                            double dt, int64_t steps, double* u, double* scratch, hipStream_t st) {
-  // Substeps per launch: more of them share one launch, its loads and its
-  // stores (8 us measured), but widen the recomputed halo and so the number
-  // of tiles (0.89 us a substep for each round of tiles over the 256 compute
-  // units).  40 fields of 128 x 128, us a substep: halo 4 2.87, 8 1.89,
-  // 16 1.39, 24 1.36, 28 2.24 (more than one tile per compute unit).  A field
-  // that is one tile needs no halo and runs its substeps in place, 0.89 us
-  // each, up to 4,096 per launch.
+// Launches of the tile kernel for a number of substeps: between tiles they
+// alternate u -> scratch -> u, an even number of them.
+static int64_t fd2d_launches(int halo, int64_t steps) {
+  return halo == 0 ? (steps + 4095) / 4096 : ((steps + halo - 1) / halo + 1) / 2 * 2;
+}
+
+// Halo of the tiles (0: a field is one tile), or -1 where a launch per substep
+// is faster.  Either kind of launch takes about 4 us and 4 us per million
+// nodes (loads and stores); tiles add 0.89 us per substep for each round of
+// tiles over the 256 compute units, however few of a tile's nodes there are.
+// Measured, us a substep by launches and by tiles: 16,384 fields of 16 x 16
+// 18.2 and 58.7, 4,096 of 32 x 32 17.3 and 14.5; 2,048 of 8 x 8 3.8 and 7.5,
+// 300 of 16 x 16 3.9 and 1.9; one field of 100,000 x 8 6.0 and 12.0.  Two
+// substeps of 200 fields of 128 x 128: 32 and 40 us, three: 59 and 42.
+static int fd2d_halo(int64_t nx, int64_t ny, int64_t n_grid, int64_t steps) {
+  auto tiles = [&](int h) { return (double)fd_tiles(nx, FD_ROWS, h) * (double)fd_tiles(ny, FD_COLS, h) * (double)n_grid; };
+  auto rounds = [&](int h) { return ceil(tiles(h) / 256.0); };
+  // Substeps per launch: more of them share one launch, but widen the
+  // recomputed halo and so the number of tiles.  A field that is one tile
+  // needs no halo and runs its substeps in place, up to 4,096 per launch.
   int halo = 0;
-  int64_t sub = steps;
   if (fd_tiles(nx, FD_ROWS, 0) * fd_tiles(ny, FD_COLS, 0) > 1) {
     double best = 0.0;
     for (int h : {8, 12, 16, 20, 24, 28}) {
-      const int64_t t = fd_tiles(nx, FD_ROWS, h) * fd_tiles(ny, FD_COLS, h) * n_grid;
-      const double cost = 0.89 * (double)((t + 255) / 256) + 8.0 / h;
+      const double cost = 0.89 * rounds(h) + 8.0 / h;
       if (halo == 0 || cost < best) {
         best = cost;
         halo = h;
       }
     }
-    sub = halo;
   }
+  const double launch = 4.0 + 4e-6 * (double)nx * (double)ny * (double)n_grid;
+  const double by_tiles = (double)fd2d_launches(halo, steps) * launch + 0.89 * rounds(halo) * (double)steps;
+  const double by_steps = (double)(steps + steps % 2) * launch;  // an odd number ends with a copy
+  return by_tiles <= by_steps && tiles(halo) < 2147483648.0 ? halo : -1;
+}
+
+static crom_status fd2d_run(int halo, int64_t nx, int64_t ny, int64_t n_grid, const double* nu, int nu_per_node, double dx2,
+                            double dt, int64_t steps, double* u, double* scratch, hipStream_t st) {
   Fd2dArgs a{};
   a.nu = nu;
   a.nx = nx;
   a.ny = ny;
   const int64_t nty = fd_tiles(ny, FD_COLS, halo), per_field = fd_tiles(nx, FD_ROWS, halo) * nty;
-  if (per_field * n_grid > 0x7fffffff) return fail(CROM_ERR_INVALID_ARG, "too many nodes");
   a.nty = (uint32_t)nty;
   a.per_field = (uint32_t)per_field;
   a.tiles = (uint32_t)(per_field * n_grid);
@@ -283,9 +319,7 @@ static crom_status fd2d_run(int64_t nx, int64_t ny, int64_t n_grid, const double
   a.yh = 1.0 / dx2;
   a.yl = fma(-a.yh, dx2, 1.0) / dx2;
   const uint32_t grid = a.tiles < 65536 ? a.tiles : 65536;
-  // between tiles the launches alternate u -> scratch -> u, an even number
-  // of them (the substeps shared out evenly), so that the result ends in u
-  const int64_t launches = halo == 0 ? (steps + 4095) / 4096 : ((steps + sub - 1) / sub + 1) / 2 * 2;
+  const int64_t launches = fd2d_launches(halo, steps);  // the substeps shared out evenly
   for (int64_t l = 0; l < launches; ++l) {
     a.u = halo == 0 || l % 2 == 0 ? u : scratch;
     a.v = halo == 0 || l % 2 == 1 ? u : scratch;
@@ -315,15 +349,22 @@ crom_status crom_fd_heat(int32_t dim, const int64_t* shape, int64_t n_grid, cons
   if (!u || !scratch || !nu) return fail(CROM_ERR_INVALID_ARG, "u, scratch and nu are required");
   hipStream_t st = static_cast<hipStream_t>(stream);
   const double dx2 = dx * dx;
-  if (dim == 2) return fd2d_run(nx, ny, n_grid, nu, nu_per_node, dx2, dt, steps, u, scratch, st);
+  if (dim == 2) {
+    const int halo = fd2d_halo(nx, ny, n_grid, steps);
+    if (halo >= 0) return fd2d_run(halo, nx, ny, n_grid, nu, nu_per_node, dx2, dt, steps, u, scratch, st);
+  }
   const int threads = 256;
   int64_t blocks = (total + threads - 1) / threads;
   if (blocks > 65536) blocks = 65536;
   double* a = u;
   double* b = scratch;
   for (int64_t s = 0; s < steps; ++s) {
-    hipLaunchKernelGGL(fd1d_kernel, dim3((unsigned)blocks), dim3(threads), 0, st, a, b, nu, nu_per_node, nx, n_grid,
-                       dt, dx2);
+    if (dim == 1)
+      hipLaunchKernelGGL(fd1d_kernel, dim3((unsigned)blocks), dim3(threads), 0, st, a, b, nu, nu_per_node, nx, n_grid,
+                         dt, dx2);
+    else
+      hipLaunchKernelGGL(fd2d_step_kernel, dim3((unsigned)blocks), dim3(threads), 0, st, a, b, nu, nu_per_node, nx, ny,
+                         n_grid, dt, dx2);
     double* t = a;
     a = b;
     b = t;

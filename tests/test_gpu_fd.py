@@ -98,3 +98,49 @@ def test_fd2d_overflow(cuda, dx, amp):
         with np.errstate(all="ignore"):
             ref = heat.fd_heat2d(u0[0], 1.0, dx, dt, 90)
         np.testing.assert_array_equal(u[0].cpu().numpy(), ref)
+
+
+# one launch per substep: many small fields (from 1,024 tiles on), narrow ones,
+# one or two substeps of several tiles; and the neighbours of each that tiles take
+@pytest.mark.parametrize("per_node", [False, True])
+@pytest.mark.parametrize("n_grid,nx,ny,steps", [(1536, 3, 2, 9), (1536, 5, 6, 8), (1024, 8, 8, 7), (1, 40000, 5, 12),
+                                                (1, 130, 257, 1), (1, 130, 257, 2), (1, 130, 257, 3), (2, 64, 129, 2),
+                                                (700, 1, 4, 33), (3, 64, 128, 1)])
+def test_fd2d_routes_bit_exact(cuda, n_grid, nx, ny, steps, per_node):
+    import torch
+    from paper_2206_02607_amd import crom
+    g = rng(nx * 1000 + ny + steps)
+    u0 = g.uniform(-1, 1, size=(n_grid, nx, ny)) * 10.0 ** g.integers(-250, 3, size=(n_grid, nx, ny))
+    nu = g.uniform(0.1, 1.0, size=(n_grid, nx, ny) if per_node else n_grid)
+    dx = 1.0 / 126.7
+    dt = 0.2 * dx * dx
+    u = torch.from_numpy(u0.copy()).to(cuda)
+    crom.fd_heat(u, torch.from_numpy(np.ascontiguousarray(nu)).to(cuda), dx, dt, steps)
+    got = u.cpu().numpy()
+    for k in range(0, n_grid, max(1, n_grid // 50)):
+        np.testing.assert_array_equal(got[k], heat.fd_heat2d(u0[k], nu[k], dx, dt, steps))
+
+
+def test_fd2d_small_fields_cost(cuda):
+    """A substep of many small fields is a pass over their memory, not a
+    workgroup's tile for each: at most 2.5 times a copy (about 1.3)."""
+    import torch
+    from paper_2206_02607_amd import crom
+    u = torch.rand(16384, 16, 16, dtype=torch.float64, device=cuda)
+    v, nu, steps = torch.empty_like(u), torch.ones(16384, dtype=torch.float64, device=cuda), 40
+
+    def us(f, n):
+        best = 1e30
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(n):
+                f()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3 / n)
+        return best
+
+    sub, copy = us(lambda: crom.fd_heat(u, nu, 0.01, 1e-6, steps, v), 2) / steps, us(lambda: v.copy_(u), steps)
+    print(f"substep {sub:.1f} us, copy {copy:.1f} us")
+    assert sub < 2.5 * copy, (sub, copy)
