@@ -474,6 +474,17 @@ static int64_t fused_chunk_rows(int64_t P, int B, bool vjp) {
   return (P + row_chunks(P, B) - 1) / row_chunks(P, B);
 }
 
+// The most chunks fused_chunk_rows leaves for any smaller B and P too: what
+// the workspace is sized for, so that it holds a smaller last batch.
+template <class T>
+static int64_t fused_max_items(int64_t P, int B, bool vjp) {
+  constexpr int ROWS = FusedTile<T>::ROWS;
+  const int64_t blocks = (P + ROWS - 1) / ROWS * B;
+  const int64_t chunks = std::min<int64_t>((P + 255) / 256 * B, std::max(COLSUM_CHUNKS, B));
+  const int64_t single = sizeof(T) == 4 ? 8 * TF_MAX_WG : vjp ? TF_MAX_WG : 0;  // blocks that are a chunk each
+  return std::min(blocks, std::max(chunks, single));
+}
+
 // The decoder's forward and backward over B snapshots x P points.  q: [B][r]
 // FP32 latents.  dg_in: when not NULL the caller's dL/dg [B*P][D] (no loss);
 // otherwise u [B][P] gives the MSE loss and dL/dg.  Writes grad_dec (natural
@@ -487,18 +498,17 @@ struct DecoderPass {
   void* frags;  // the fused pass: packed weights, sums carried between blocks, first activations
   f32x4* carry;
   T* a0;
-  static size_t bytes(const crom_net* n, int B, int64_t P) {
+  static size_t vjp_bytes(const crom_net* n, int B, int64_t P) {
     Carve cv{nullptr, 0};
     DecoderPass d;
-    d.carve(cv, n, B, P);
+    d.carve(cv, n, B, P, true);
     return cv.off;
   }
-  void carve(Carve& cv, const crom_net* n, int B, int64_t P) {
+  void carve(Carve& cv, const crom_net* n, int B, int64_t P, bool vjp) {
     const int64_t rows = (int64_t)B * P;
     const int W = n->width, depth = n->depth, D = n->d;
     if (fused_shape(n)) {
-      const int64_t rows = std::min(fused_chunk_rows<T>(P, B, true), fused_chunk_rows<T>(P, B, false));
-      const int64_t items = (P + rows - 1) / rows * B, wgs = items < TF_MAX_WG ? items : TF_MAX_WG;
+      const int64_t items = fused_max_items<T>(P, B, vjp), wgs = items < TF_MAX_WG ? items : TF_MAX_WG;
       frags = cv.take<f32x4>((size_t)(depth - 1) * 2 * FusedTile<T>::FRAGS);
       c = cv.take<float>((size_t)B * W);
       part = cv.take<float>((size_t)wgs * (depth - 1) * TF_MAT);
@@ -1218,7 +1228,7 @@ template <class T>
 static size_t train_bytes_t(const crom_net* n, const crom_encoder* e, int B) {
   Carve cv{nullptr, 0};
   DecoderPass<T> d;
-  d.carve(cv, n, B, e->n_in / n->d);
+  d.carve(cv, n, B, e->n_in / n->d, false);
   if (e->kind == CROM_ENC_CONV) {
     ConvPass cp;
     cp.carve(cv, conv_of(n, e), B);
@@ -1246,7 +1256,7 @@ static crom_status train_grads_t(const crom_net* n, const crom_encoder* e, const
   Carve cv{reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255)), 0};
   const int64_t P = e->n_in / n->d;
   DecoderPass<T> d;
-  d.carve(cv, n, B, P);
+  d.carve(cv, n, B, P, false);
   if (e->kind == CROM_ENC_CONV) {
     const ConvShape c = conv_of(n, e);
     ConvPass cp;
@@ -1453,7 +1463,7 @@ crom_status crom_decode_vjp_workspace(const crom_net* net, int32_t B, int64_t P,
       (net->act != CROM_ACT_SINE || net->precision == CROM_PREC_FP32 || (net->width != 32 && net->width != 128)))
     return fail(CROM_ERR_UNSUPPORTED, "training kernels: ELU networks, or sine networks of width 32 or 128 in bfloat16");
   if (B < 1 || P < 1 || !bytes) return fail(CROM_ERR_INVALID_ARG, "B >= 1, P >= 1 and bytes are required");
-  *bytes = (bf_mode(net) ? DecoderPass<__bf16>::bytes(net, B, P) : DecoderPass<float>::bytes(net, B, P)) + 256;
+  *bytes = (bf_mode(net) ? DecoderPass<__bf16>::vjp_bytes(net, B, P) : DecoderPass<float>::vjp_bytes(net, B, P)) + 256;
   return CROM_OK;
 }
 
@@ -1475,11 +1485,11 @@ crom_status crom_decode_vjp(const crom_net* net, const float* x, int64_t P, cons
   Carve cv{reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255)), 0};
   if (bf_mode(net)) {
     DecoderPass<__bf16> d;
-    d.carve(cv, net, B, P);
+    d.carve(cv, net, B, P, true);
     return decoder_fwd_bwd<__bf16>(net, x, B, P, q, nullptr, dg, grad_params, grad_q, nullptr, d, st);
   }
   DecoderPass<float> d;
-  d.carve(cv, net, B, P);
+  d.carve(cv, net, B, P, true);
   return decoder_fwd_bwd<float>(net, x, B, P, q, nullptr, dg, grad_params, grad_q, nullptr, d, st);
 }
 

@@ -218,3 +218,27 @@ def test_step_workspace_at_the_static_limit(shape, samples):
     n = ctypes.c_size_t(0)
     assert L.crom_step_workspace(ctypes.byref(_net(**shape)), 1, samples, ctypes.byref(n)) == 0
     assert n.value <= L.crom_step_static_capacity() == 64 << 20
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_training_workspace_grows_with_the_batch(precision):
+    """A workspace sized for a batch holds every smaller one, in snapshots and
+    in points, across the places where the fused pass changes its chunks."""
+    L = crom.lib()
+    net, n = _net(precision=precision), ctypes.c_size_t(0)
+
+    def train(B, P, kind=0):
+        assert L.crom_train_workspace(ctypes.byref(net), ctypes.byref(crom.CromEncoder(P, 32, 8, kind, 1 << 22)), B,
+                                      ctypes.byref(n)) == 0
+        return n.value
+
+    def vjp(B, P):
+        assert L.crom_decode_vjp_workspace(ctypes.byref(net), B, P, ctypes.byref(n)) == 0
+        return n.value
+
+    points = [1, 63, 64, 65, 127, 128, 129, 255, 256, 257, 385, 1000, 4999, 8192, 10000, 16384, 16385, 32768, 65536, 131073,
+              255000, 255001, 524288, 600000]
+    batches = list(range(1, 40)) + [63, 64, 65, 255, 256, 257, 300, 682, 683, 2047, 2048, 2049, 3000]
+    for query in (train, vjp, lambda B, P: train(B, max(P, 200), 1)):
+        sizes = np.array([[query(B, P) for P in points] for B in batches], np.int64)
+        assert (np.diff(sizes, axis=0) >= 0).all() and (np.diff(sizes, axis=1) >= 0).all()
