@@ -762,9 +762,9 @@ __global__ __launch_bounds__(256) void enc_part_kernel(const float* __restrict__
   constexpr int STEP = BF ? 32 : 4, E = STEP / 4;  // K of one product; K per lane
   typedef T frag __attribute__((ext_vector_type(E)));
   const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
-  const int n0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * 16, b0 = blockIdx.z * 16;
+  const int bt = (B + 15) / 16, b0 = (int)(blockIdx.x % bt) * 16, n0 = ((int)(blockIdx.x / bt) * 4 + (threadIdx.x >> 6)) * 16;
   if (n0 >= N) return;
-  const int64_t k0 = blockIdx.x * kchunk, k1 = k0 + kchunk < K ? k0 + kchunk : K;
+  const int64_t k0 = blockIdx.y * kchunk, k1 = k0 + kchunk < K ? k0 + kchunk : K;
   auto load = [&](const float* row, bool ok, int64_t k) {
     frag f;
     if constexpr (BF) {
@@ -806,7 +806,7 @@ __global__ __launch_bounds__(256) void enc_part_kernel(const float* __restrict__
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int row = b0 + 4 * lg + v;
-    if (row < B && n < N) part[((int64_t)blockIdx.x * B + row) * N + n] = acc[v];
+    if (row < B && n < N) part[((int64_t)blockIdx.y * B + row) * N + n] = acc[v];
   }
 }
 
@@ -816,7 +816,7 @@ __global__ __launch_bounds__(64) void enc_latent_kernel(const float* __restrict_
                                                         const float* __restrict__ c2, int B, int r, int K,
                                                         float* __restrict__ q, float* __restrict__ q2) {
   const int lr = threadIdx.x & 15, lg = threadIdx.x >> 4;
-  const int b = blockIdx.y * 16 + lr, n = blockIdx.x * 16 + lr;
+  const int b = blockIdx.x * 16 + lr, n = blockIdx.y * 16 + lr;
   f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
   constexpr int U = 16;  // products whose operands are in flight together
   for (int k0 = 0; k0 < K; k0 += 4 * U) {
@@ -832,7 +832,7 @@ __global__ __launch_bounds__(64) void enc_latent_kernel(const float* __restrict_
   }
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    const int row = blockIdx.y * 16 + 4 * lg + v;
+    const int row = blockIdx.x * 16 + 4 * lg + v;
     if (row < B && n < r) {
       const float t = acc[v] + c2[n];
       q[row * r + n] = t;
@@ -854,14 +854,13 @@ static crom_status encoder_fwd(const crom_encoder* e, const float* u, int B, Enc
   const int64_t kc = (((int64_t)e->n_in + splits - 1) / splits + BK - 1) / BK * BK;
   splits = (e->n_in + kc - 1) / kc;
   const int vec = e->n_in % 4 == 0 && (reinterpret_cast<uintptr_t>(u) | reinterpret_cast<uintptr_t>(prm)) % 16 == 0;
-  if ((B + 15) / 16 > 65535) return fail(CROM_ERR_UNSUPPORTED, "too many snapshots");
-  hipLaunchKernelGGL(enc_part_kernel<T>, dim3((unsigned)splits, (e->hidden + 63) / 64, (B + 15) / 16), dim3(256), 0, st,
-                     u, prm, B, e->hidden, (int64_t)e->n_in, kc, vec, ws.ub, ws.kpart);
+  hipLaunchKernelGGL(enc_part_kernel<T>, dim3((unsigned)((int64_t)((B + 15) / 16) * ((e->hidden + 63) / 64)), (unsigned)splits),
+                     dim3(256), 0, st, u, prm, B, e->hidden, (int64_t)e->n_in, kc, vec, ws.ub, ws.kpart);
   hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)(((int64_t)B * e->hidden + 63) / 64)), dim3(256), 0, st,
                      ws.kpart, (int)splits, B, e->hidden, ws.h32, (int64_t)e->hidden, 0, (int)EPI_BIAS_ELU,
                      prm + pi.b[0]);
   // q = h E2^T + c2 (FP32 product of the FP32 activations)
-  hipLaunchKernelGGL(enc_latent_kernel, dim3((e->r + 15) / 16, (B + 15) / 16), dim3(64), 0, st, ws.h32, prm + pi.w[1],
+  hipLaunchKernelGGL(enc_latent_kernel, dim3((B + 15) / 16, (e->r + 15) / 16), dim3(64), 0, st, ws.h32, prm + pi.w[1],
                      prm + pi.b[1], B, e->r, e->hidden, ws.q, q_out);
   return hip_check(hipGetLastError(), "encoder forward");
 }

@@ -566,3 +566,19 @@ def test_bias_gradient_sums_in_64_bits(cuda, depth, prec):
     np.testing.assert_array_equal(got[-1][1], np.full(1, total, np.float32))
     for l in range(depth):
         np.testing.assert_array_equal(got[l][1], np.full(W, total / 2, np.float32), err_msg=f"layer {l}")
+
+
+def test_dense_encoder_million_snapshots(cuda):
+    """More snapshots than 65,535 tiles of 16 (encoder forward)."""
+    import torch
+    B, P = 1_048_577, 4
+    dec, enc, x, u, m = _problem("1d", 18, 3, P, 1)
+    D, T = _trainer(dec, enc, x, u, m, "fp32", cuda, hidden=1)
+    big = rng(19).uniform(-1, 1, size=(B, P)).astype(np.float32)
+    q = T.encode(torch.from_numpy(big).to(cuda)).cpu().numpy()
+    (E1, c1), (E2, c2) = enc
+    z = big.astype(np.float64) @ np.asarray(E1, np.float32).astype(np.float64).T + np.asarray(c1, np.float32)
+    h = np.where(z > 0, z, np.expm1(np.minimum(z, 0)))
+    ref = h @ np.asarray(E2, np.float32).astype(np.float64).T + np.asarray(c2, np.float32)
+    assert normwise_rel(q, ref) <= TOL["fp32"]
+    assert normwise_rel(q[-20:], ref[-20:]) <= TOL["fp32"]
