@@ -866,34 +866,40 @@ static crom_status encoder_fwd(const crom_encoder* e, const float* u, int B, Enc
 }
 
 // Backward of the dense encoder's small layers, one wave per 16 hidden units
-// (nine launches of the general products and sums took 60 us for 16 snapshots
-// and 256 units):
+// and chunk of snapshots (nine launches of the general products and sums took
+// 60 us for 16 snapshots and 256 units):
 //   dz1 [B][hidden] = (dq E2) * ELU'(h), in T (FP32 products in K order),
 //   dc1 = sum_b dz1,  dE2 [r][hidden] = dq^T h,  dc2 = sum_b dq  (FP64 sums).
+// A wave takes 4 us for every 16 snapshots, a chain of dependent loads: all
+// 100,000 in one wave took 23 ms.  One chunk writes the gradients; of several, each
+// leaves its sums in part [chunk][N (1 + r) + r] (dc1, dE2, dc2), which
+// enc_bwd_final_kernel adds up.
 template <class T>
 __global__ __launch_bounds__(64) void enc_bwd_kernel(const float* __restrict__ dq, const float* __restrict__ E2,
-                                                     const float* __restrict__ h, int B, int r, int N,
+                                                     const float* __restrict__ h, int B, int chunk, int r, int N,
                                                      T* __restrict__ dz1, float* __restrict__ dc1,
-                                                     float* __restrict__ dE2, float* __restrict__ dc2) {
+                                                     float* __restrict__ dE2, float* __restrict__ dc2,
+                                                     double* __restrict__ part) {
   constexpr int RM = 16;  // largest latent size
   const int lr = threadIdx.x & 15, lg = threadIdx.x >> 4;
   const int n = blockIdx.x * 16 + lr;
+  const int c0 = blockIdx.y * chunk, c1 = B - c0 < chunk ? B : c0 + chunk;
   double s1 = 0.0, s2[RM];
 #pragma unroll
   for (int k = 0; k < RM; ++k) s2[k] = 0.0;
-  for (int b0 = 0; b0 < B; b0 += 16) {
+  for (int b0 = c0; b0 < c1; b0 += 16) {
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int k0 = 0; k0 < RM; k0 += 4) {
       const int k = k0 + lg;
-      const float x = b0 + lr < B && k < r ? dq[(b0 + lr) * r + k] : 0.0f;
+      const float x = b0 + lr < c1 && k < r ? dq[(b0 + lr) * r + k] : 0.0f;
       const float y = n < N && k < r ? E2[(int64_t)k * N + n] : 0.0f;
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, acc, 0, 0, 0);
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int b = b0 + 4 * lg + v;
-      if (b >= B || n >= N) continue;
+      if (b >= c1 || n >= N) continue;
       const float hv = h[(int64_t)b * N + n], z = acc[v] * elu_d1_from_a(hv);
       dz1[(int64_t)b * N + n] = (T)z;
       s1 += (double)z;
@@ -906,28 +912,60 @@ __global__ __launch_bounds__(64) void enc_bwd_kernel(const float* __restrict__ d
     s += __shfl_xor(s, 16);
     return s + __shfl_xor(s, 32);
   };
+  double* p = gridDim.y > 1 ? part + blockIdx.y * ((int64_t)N * (1 + r) + r) : nullptr;
   s1 = groups(s1);
 #pragma unroll
   for (int k = 0; k < RM; ++k) s2[k] = groups(s2[k]);
   if (lg == 0 && n < N) {
-    dc1[n] = (float)s1;
+    if (p) p[n] = s1;
+    else dc1[n] = (float)s1;
 #pragma unroll
-    for (int k = 0; k < RM; ++k)
-      if (k < r) dE2[(int64_t)k * N + n] = (float)s2[k];
+    for (int k = 0; k < RM; ++k) {
+      if (k >= r) continue;
+      if (p) p[(int64_t)N * (1 + k) + n] = s2[k];
+      else dE2[(int64_t)k * N + n] = (float)s2[k];
+    }
   }
   if (blockIdx.x == 0 && threadIdx.x < r) {
     double s = 0.0;
-    for (int b = 0; b < B; ++b) s += (double)dq[b * r + threadIdx.x];
-    dc2[threadIdx.x] = (float)s;
+    for (int b = c0; b < c1; ++b) s += (double)dq[b * r + threadIdx.x];
+    if (p) p[(int64_t)N * (1 + r) + threadIdx.x] = s;
+    else dc2[threadIdx.x] = (float)s;
   }
+}
+
+// One wave per gradient, its lanes over the chunks.
+__global__ __launch_bounds__(256) void enc_bwd_final_kernel(const double* __restrict__ part, int chunks, int r, int N,
+                                                            float* __restrict__ dc1, float* __restrict__ dE2,
+                                                            float* __restrict__ dc2) {
+  const int64_t n_out = (int64_t)N * (1 + r) + r, o = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (o >= n_out) return;
+  double s = 0.0;
+  for (int c = lane; c < chunks; c += 64) s += part[c * n_out + o];
+#pragma unroll
+  for (int w = 1; w < 64; w <<= 1) s += __shfl_xor(s, w);
+  if (lane != 0) return;
+  if (o < N) dc1[o] = (float)s;
+  else if (o < (int64_t)N * (1 + r)) dE2[o - N] = (float)s;
+  else dc2[o - (int64_t)N * (1 + r)] = (float)s;
 }
 
 template <class T>
 static crom_status encoder_bwd(const crom_encoder* e, const float* u, int B, const float* dq, float* grad,
                                EncoderPass<T>& ws, hipStream_t st) {
   const ParamIndex pi = enc_index(e);
-  hipLaunchKernelGGL(enc_bwd_kernel<T>, dim3((e->hidden + 15) / 16), dim3(64), 0, st, dq, e->params + pi.w[1], ws.h32, B,
-                     e->r, e->hidden, ws.dh, grad + pi.b[0], grad + pi.w[1], grad + pi.b[1]);
+  // chunks of 64 snapshots, of more where there would be over 1,024; their
+  // sums take the place of the forward's partial products, MAX_SPLITS FP32
+  // values for each of the B x hidden
+  const int chunk = std::max(64, ((B - 1) / 1024 + 16) / 16 * 16), chunks = (B - 1) / chunk + 1;
+  static_assert((1 + 2 * 16) * 8 <= MAX_SPLITS * 4 * 64, "a chunk's sums fit (r <= 16, one unit)");
+  double* part = reinterpret_cast<double*>(ws.kpart);
+  hipLaunchKernelGGL(enc_bwd_kernel<T>, dim3((e->hidden + 15) / 16, chunks), dim3(64), 0, st, dq, e->params + pi.w[1],
+                     ws.h32, B, chunk, e->r, e->hidden, ws.dh, grad + pi.b[0], grad + pi.w[1], grad + pi.b[1], part);
+  if (chunks > 1)
+    hipLaunchKernelGGL(enc_bwd_final_kernel, dim3((unsigned)(((int64_t)e->hidden * (1 + e->r) + e->r + 3) / 4)), dim3(256),
+                       0, st, part, chunks, e->r, e->hidden, grad + pi.b[0], grad + pi.w[1], grad + pi.b[1]);
   // dE1 = dz1^T u  [hidden][n_in]
   const void* ut = ws.ub ? static_cast<const void*>(ws.ub) : u;
   GemmArgs g = gemm_args(e->hidden, e->n_in, B, ws.dh, e->hidden, ut, e->n_in);

@@ -568,6 +568,23 @@ def test_bias_gradient_sums_in_64_bits(cuda, depth, prec):
         np.testing.assert_array_equal(got[l][1], np.full(W, total / 2, np.float32), err_msg=f"layer {l}")
 
 
+# the dense encoder's backward in chunks of 64 snapshots: one, two, many, a short last one
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("B,P,hidden", [(64, 40, 17), (65, 40, 17), (1000, 9, 24), (70000, 2, 1)])
+def test_dense_encoder_many_snapshots(cuda, B, P, hidden, prec):
+    import torch
+    dec, enc, x, u, m = _problem("1d", 17, B, P, hidden)
+    D, T = _trainer(dec, enc, x, u, m, prec, cuda, hidden=hidden)
+    loss, gd, ge, q = T.grads(torch.from_numpy(u).to(cuda))
+    rl, rgd, rge, rq = train.loss_and_grads(*_as_held(dec, enc, prec), x, u)
+    errs = {"q": normwise_rel(q.cpu().numpy(), rq)}
+    for li, ((gW, gb), (rW, rb)) in enumerate(zip(_split(ge.cpu().numpy(), enc), rge)):
+        errs[f"W{li}"] = normwise_rel(gW, rW)
+        errs[f"b{li}"] = normwise_rel(gb, rb)
+    bad = {k: v for k, v in errs.items() if not v <= TOL[prec]}
+    assert not bad, bad
+
+
 def test_dense_encoder_million_snapshots(cuda):
     """More snapshots than 65,535 tiles of 16 (encoder forward)."""
     import torch
@@ -582,3 +599,32 @@ def test_dense_encoder_million_snapshots(cuda):
     ref = h @ np.asarray(E2, np.float32).astype(np.float64).T + np.asarray(c2, np.float32)
     assert normwise_rel(q, ref) <= TOL["fp32"]
     assert normwise_rel(q[-20:], ref[-20:]) <= TOL["fp32"]
+
+
+def test_dense_encoder_backward_cost(cuda):
+    """The encoder's backward is a small part of the gradients of 20,000 small
+    snapshots, not a serial walk over them (three times the rest)."""
+    import torch
+    from paper_2206_02607_amd import crom
+    B, P, hidden = 20000, 16, 64
+    dec, enc, x, u, m = _problem("1d", 20, 2, P, hidden)
+    D, T = _trainer(dec, enc, x, np.zeros((B, P), np.float32), m, "bf16", cuda, hidden=hidden)
+    big = torch.from_numpy(rng(21).uniform(-1, 1, size=(B, P)).astype(np.float32)).to(cuda)
+    xt, dg = torch.from_numpy(x).to(cuda), torch.ones(B, P, 1, device=cuda)
+    q = T.encode(big)
+
+    def us(f):
+        best = 1e30
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            f()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3)
+        return best
+
+    whole = us(lambda: T.grads(big))
+    rest = us(lambda: crom.decode_vjp(D, xt, q, dg)) + us(lambda: T.encode(big))
+    print(f"gradients {whole:.0f} us, decoder and encoder forward {rest:.0f} us")
+    assert whole < 2 * rest
