@@ -553,6 +553,8 @@ crom_status crom_decode(const crom_net* net, const float* x, int64_t P, const do
 crom_status crom_decode_batch(const crom_net* net, const float* x, int64_t P, const double* q, int32_t B, float* g,
                               void* stream) {
   if (B < 0) return crom::fail(CROM_ERR_INVALID_ARG, "B < 0");
+  const crom_status ok = check_net(net, true);
+  if (ok != CROM_OK) return ok;
   if (B == 0) return decode_any(net, x, 0, q, 1, CROM_D2_NONE, g, nullptr, nullptr, nullptr, stream);
   constexpr int CHUNK = 32768;  // the grid's second dimension
   for (int32_t b = 0; b < B; b += CHUNK) {

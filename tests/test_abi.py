@@ -242,3 +242,17 @@ def test_training_workspace_grows_with_the_batch(precision):
     for query in (train, vjp, lambda B, P: train(B, max(P, 200), 1)):
         sizes = np.array([[query(B, P) for P in points] for B in batches], np.int64)
         assert (np.diff(sizes, axis=0) >= 0).all() and (np.diff(sizes, axis=1) >= 0).all()
+
+
+def test_decode_batch_validation():
+    L = crom.lib()
+    assert L.crom_decode_batch(None, 1, 10, 1, 2, 1, None) == L.crom_decode(None, 1, 10, 1, 1, None) == 1
+    bad = _net(width=96)
+    assert L.crom_decode_batch(ctypes.byref(bad), 1, 10, 1, 2, 1, None) == L.crom_decode(ctypes.byref(bad), 1, 10, 1, 1, None)
+    net = _net()
+    assert L.crom_decode_batch(ctypes.byref(net), 1, 10, 1, -1, 1, None) == 1
+    assert L.crom_decode_batch(ctypes.byref(net), 1, -1, 1, 2, 1, None) == 1
+    for args in ((None, 10, 1, 2, 1), (1, 10, None, 2, 1), (1, 10, 1, 2, None)):
+        assert L.crom_decode_batch(ctypes.byref(net), *args, None) == 1
+    assert L.crom_decode_batch(ctypes.byref(net), None, 0, None, 3, None, None) == 0  # no points
+    assert L.crom_decode_batch(ctypes.byref(net), None, 10, None, 0, None, None) == 0  # no latents
