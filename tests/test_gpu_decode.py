@@ -179,6 +179,46 @@ def test_fp32_jacobian_paths(cuda, shape, depth, P, dx, d2):
             assert normwise_rel(a.cpu().numpy().reshape(b.shape), b) <= TOL["fp32"]
 
 
+# The 3D Hessian runs in chunks of its own passes, the latent Jacobian beside it
+# in the reverse pass (depths 2 to 6) or in forward tangents (7)
+@pytest.mark.parametrize("depth,P,dx", [(2, 17, True), (5, 1, True), (6, 33, True), (6, 16, False), (7, 18, True)])
+def test_fp32_hessian_with_jacobian_3d(cuda, depth, P, dx):
+    import torch
+    from paper_2206_02607_amd import crom
+    g = rng(700 + depth + P)
+    layers = xavier_mlp(g, 3, 16, 3, 256, depth, bias_scale=0.2)
+    dec = crom.Decoder.from_layers(layers, 3, precision="fp32", device=cuda)
+    x, q = uniform_points(g, P, 3), g.uniform(-1, 1, size=16)
+    got = dec.decode_jac(torch.from_numpy(x).to(cuda), torch.from_numpy(q).to(cuda), dx=dx, d2=crom.D2_HESSIAN, dq=True)
+    og, ogx, oh, ogq = mlp.decode_jets(layers, x, q, 3)
+    for a, b in zip(got, (og, ogx if dx else None, mlp.hessian_packed(oh), ogq)):
+        assert (a is None) == (b is None)
+        if a is not None:
+            assert normwise_rel(a.cpu().numpy().reshape(b.shape), b) <= TOL["fp32"]
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("d2", ["none", "lap", "hess"])
+def test_fp32_jacobian_nonfinite_points(cuda, d2, bad):
+    """A point that is not finite spoils its own rows and no other point's."""
+    import torch
+    from paper_2206_02607_amd import crom
+    g = rng(77)
+    layers = xavier_mlp(g, 2, 8, 1, 128, 5, bias_scale=0.2)
+    dec = crom.Decoder.from_layers(layers, 2, precision="fp32", device=cuda)
+    x, q = torch.from_numpy(uniform_points(g, 40, 2)).to(cuda), torch.from_numpy(g.uniform(-1, 1, size=8)).to(cuda)
+    mode = {"none": crom.D2_NONE, "lap": crom.D2_LAPLACIAN, "hess": crom.D2_HESSIAN}[d2]
+    ref = dec.decode_jac(x, q, dx=True, d2=mode, dq=True)
+    y, rows = x.clone(), [0, 21, 39]
+    y[rows, 1] = float(bad)
+    got = dec.decode_jac(y, q, dx=True, d2=mode, dq=True)
+    keep = [i for i in range(40) if i not in rows]
+    for a, b in zip(got, ref):
+        if a is not None:
+            assert torch.equal(a[keep], b[keep])
+    assert not torch.isfinite(got[0][rows]).all()
+
+
 # Value decode of many points at width 128 in BF16 (activations in registers):
 # the same products, sums and epilogues in the same order as the kernel that
 # small calls use, so the values are the same bits; batches (B latents) too.
