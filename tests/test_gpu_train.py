@@ -628,3 +628,33 @@ def test_dense_encoder_backward_cost(cuda):
     rest = us(lambda: crom.decode_vjp(D, xt, q, dg)) + us(lambda: T.encode(big))
     print(f"gradients {whole:.0f} us, decoder and encoder forward {rest:.0f} us")
     assert whole < 2 * rest
+
+
+# the fused pass in FP32: its blocks of 64 rows, every depth and latent size, and
+# (over 2,048 blocks) chunks of four blocks, whose sums are carried between them
+@pytest.mark.parametrize("depth,r,B,P", [(3, 8, 1, 1), (3, 16, 2, 63), (4, 8, 2, 64), (4, 16, 1, 65), (5, 16, 3, 129),
+                                         (3, 8, 2, 65601)])
+def test_fused_pass_edges_fp32(cuda, depth, r, B, P):
+    import torch
+    from paper_2206_02607_amd import crom
+    g = rng(1000 * depth + P)
+    dec = xavier_mlp(g, 2, r, 1, 128, depth, bias_scale=0.2)
+    enc = xavier_mlp(g, P, 0, r, 24, 1, bias_scale=0.2)
+    x = uniform_points(g, P, 2)
+    u = g.uniform(-1, 1, size=(B, P)).astype(np.float32)
+    D, T = _trainer(dec, enc, x, u, 2, "fp32", cuda, hidden=24)
+    loss, gd, ge, q = T.grads(torch.from_numpy(u).to(cuda))
+    rl, rgd, rge, rq = train.loss_and_grads(dec, enc, x, u)
+    errs = {"loss": abs(loss.item() - rl) / rl, "q": normwise_rel(q.cpu().numpy(), rq)}
+    for name, got, ref, layers in (("dec", gd, rgd, dec), ("enc", ge, rge, enc)):
+        for li, ((gW, gb), (rW, rb)) in enumerate(zip(_split(got.cpu().numpy(), layers), ref)):
+            errs[f"{name}W{li}"] = normwise_rel(gW, rW)
+            errs[f"{name}b{li}"] = normwise_rel(gb, rb)
+    # the same cotangent through the vector-Jacobian product
+    xt, ut = torch.from_numpy(x).to(cuda), torch.from_numpy(u).to(cuda)
+    dg = 2 * (D.decode_batch(xt, q.double())[..., 0] - ut) / (B * P)
+    gp, gq = crom.decode_vjp(D, xt, q.clone(), dg.reshape(B, P, 1))
+    errs["vjp"] = normwise_rel(gp.cpu().numpy(), gd.cpu().numpy())
+    print({k: f"{v:.1e}" for k, v in errs.items()})
+    bad = {k: v for k, v in errs.items() if not v <= TOL["fp32"]}
+    assert not bad, bad
