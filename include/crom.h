@@ -278,8 +278,13 @@ enum {
   CROM_FLAG_SINGULAR = 2,  /* Cholesky pivot <= 1e-14 * max diag(J^T J)     */
   CROM_FLAG_NONFINITE = 4, /* NaN/Inf in the residual or normal equations   */
   CROM_FLAG_LS_FAIL = 8,   /* no trial step satisfied the Armijo condition  */
-  CROM_FLAG_ABORTED = 16,  /* the step kernel gave up waiting on a phase (an
-                              internal error; q_next holds the last iterate) */
+  CROM_FLAG_ABORTED = 16,  /* the step kernel gave up waiting on a phase
+                              (about two seconds; q_next holds the last
+                              iterate).  Nonlinear steps of up to 1,024
+                              batches of 16 samples, and the elastic kinds,
+                              wait for workgroups that have to be resident
+                              together: other streams' kernels that hold the
+                              device that long have this effect */
   CROM_FLAG_INVERTED = 32  /* elastic kinds: det F <= 0 at a sample that is not
                               clamped (no stress there; NONFINITE follows from
                               its NaN targets and q_next = q_n) */

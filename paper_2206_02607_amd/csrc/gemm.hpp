@@ -13,7 +13,7 @@
 
 namespace crom {
 
-enum { EPI_NONE = 0, EPI_BIAS_ELU = 1, EPI_DELU = 2, EPI_BIAS = 3 };
+enum { EPI_NONE = 0, EPI_BIAS_ELU = 1, EPI_DELU = 2 };
 
 struct GemmArgs {
   int M, N, K;
@@ -25,7 +25,7 @@ struct GemmArgs {
   int64_t ldc;
   __bf16* Cb;       // bfloat16 copy of the result (may be NULL)
   int64_t ldcb;
-  const float* bias;  // EPI_BIAS_ELU / EPI_BIAS: + bias[n]
+  const float* bias;  // EPI_BIAS_ELU: + bias[n]
   const void* gate;   // EPI_DELU: result *= ELU'(z) read from the stored a = ELU(z)
   int64_t ldg;
   int kchunk;         // split-K: K range of blockIdx.z (multiple of the K tile)
@@ -178,8 +178,6 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
         if constexpr (EPI == EPI_BIAS_ELU) {
           x += g.bias[n];
           x = x > 0.0f ? x : __expf(x) - 1.0f;
-        } else if constexpr (EPI == EPI_BIAS) {
-          x += g.bias[n];
         } else if constexpr (EPI == EPI_DELU) {
           x *= elu_d1_from_a(to_f(gate[(int64_t)m * g.ldg + n]));
         }
@@ -404,7 +402,7 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const __bf16* __restrict__ X
       for (int v = 0; v < 4; ++v) P[(mq + 16 * i + 4 * lg + v) * W + nq + 16 * j + lj] = acc[i][j][v];
 }
 
-// Sum of split-K partials, then the epilogue (none, bias, or bias + ELU)
+// Sum of split-K partials, then the epilogue (none, or bias + ELU)
 // and the FP32 store.  A block takes 64 outputs; each of its 4 lanes per
 // output adds the splits z = lane, lane + 4, ... in order, and the 4 lane
 // sums are added in lane order (a fixed order: the result is deterministic).
@@ -425,8 +423,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
   if (threadIdx.x < 64 && e < MN) {
     float t = ((sh[0][threadIdx.x] + sh[1][threadIdx.x]) + sh[2][threadIdx.x]) + sh[3][threadIdx.x];
     const int m = (int)(e / N), n = (int)(e % N);
-    if (epi == EPI_BIAS || epi == EPI_BIAS_ELU) t += bias[n];
-    if (epi == EPI_BIAS_ELU) t = t > 0.0f ? t : __expf(t) - 1.0f;
+    if (epi == EPI_BIAS_ELU) {
+      t += bias[n];
+      t = t > 0.0f ? t : __expf(t) - 1.0f;
+    }
     float* c = &C[(int64_t)m * ldc + n];
     *c = accumulate ? *c + t : t;
   }

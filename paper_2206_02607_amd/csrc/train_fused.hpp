@@ -19,10 +19,13 @@
 // fragments streaming through 32 registers from L2.  In a weight gradient
 // (K = rows; bfloat16 fragments by LDS transpose reads) it takes a 64 x 32
 // block of dW, 32 accumulators per layer; the bias gradient is a product with
-// ones, at most 32 rows in FP32 and FP64 from there.  LDS holds as many tiles of rows as there are products in one
-// direction: the last layer's activations stay in registers, dz_l takes the
-// place of a_l, and a_0, whose place dz_L takes (a fifth tile would not fit),
-// waits in memory and comes back while the upper layers' gradients are formed.
+// ones, at most 32 rows in FP32 and FP64 from there (as the layerwise column
+// sums; kept in LDS it also frees registers: 258 -> 251 us for the gradients of
+// 16 snapshots of 16,384 points, FP32 training step 303 -> 306).  LDS holds as
+// many tiles of rows as there are products in one direction: the last layer's
+// activations stay in registers, dz_l takes the place of a_l, and a_0, whose
+// place dz_L takes (a fifth tile would not fit), waits in memory and comes back
+// while the upper layers' gradients are formed.
 //
 // In bfloat16 the operands, the K order of every product, the epilogues, the
 // output layer's sum (unit order) and the sums of dz_0 (16 row groups per
@@ -76,8 +79,9 @@ struct FusedArgs {
   double* opart;              // [workgroups][tf_out(layers)]
 };
 
-// Weight fragments of every hidden-to-hidden layer (forward and transposed; the rows of a pair of M-tiles are dealt so that a lane ends
-// with 8 consecutive units: one 16-byte LDS access) and the per-snapshot fold of the first layer
+// Weight fragments of every hidden-to-hidden layer (forward and transposed; the
+// rows of a pair of M-tiles are dealt so that a lane ends with 8 consecutive
+// units: one 16-byte LDS access) and the per-snapshot fold of the first layer
 // c[b][u] = b1[u] + sum_k W1[u][2 + k] q[b][k] (FP64 accumulation).
 template <class T>
 __global__ __launch_bounds__(256) void fused_prep_kernel(const float* __restrict__ params, ParamIndex pi, int L,
