@@ -19,9 +19,9 @@
 // fragments streaming through 32 registers from L2.  In a weight gradient
 // (K = rows; bfloat16 fragments by LDS transpose reads) it takes a 64 x 32
 // block of dW, 32 accumulators per layer; the bias gradient is a product with
-// ones, at most 32 rows in FP32 and FP64 from there (as the layerwise column
-// sums; kept in LDS it also frees registers: 258 -> 251 us for the gradients of
-// 16 snapshots of 16,384 points, FP32 training step 303 -> 306).  LDS holds as
+// ones, 32 rows in FP32 and FP64 from there (the layerwise column sums: 16 or
+// 32; kept in LDS it also frees registers: 258 -> 246 us for the gradients of
+// 16 snapshots of 16,384 points, FP32 training step 301 -> 303).  LDS holds as
 // many tiles of rows as there are products in one direction: the last layer's
 // activations stay in registers, dz_l takes the place of a_l, and a_0, whose
 // place dz_L takes (a fifth tile would not fit), waits in memory and comes back
@@ -109,20 +109,33 @@ __global__ __launch_bounds__(256) void fused_prep_kernel(const float* __restrict
   }
 }
 
-// Sum over the 16 lanes of a DPP row, in every lane (rotations by 8, 4, 2, 1).
-__device__ __forceinline__ double row16_sum(double v) {
-  auto rot = [](double x, auto ctrl) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, decltype(ctrl)::value, 0xf, 0xf, false);
-    const unsigned hi =
-        (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), decltype(ctrl)::value, 0xf, 0xf, false);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-  };
-  v += rot(v, std::integral_constant<int, 0x128>{});
-  v += rot(v, std::integral_constant<int, 0x124>{});
-  v += rot(v, std::integral_constant<int, 0x122>{});
-  v += rot(v, std::integral_constant<int, 0x121>{});
-  return v;
+// Sum over the 16 lanes of a DPP row, in every lane (rotations by 8, 4, 2, 1):
+// the first STEPS rotations' sums in FP32, the others in FP64.
+template <int CTRL>
+__device__ __forceinline__ unsigned row_rot(unsigned v) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL, class V>
+__device__ __forceinline__ V plus_rot(V v) {
+  if constexpr (sizeof(V) == 4) {
+    return v + __uint_as_float(row_rot<CTRL>(__float_as_uint(v)));
+  } else {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = row_rot<CTRL>((unsigned)b), hi = row_rot<CTRL>((unsigned)(b >> 32));
+    return v + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+  }
+}
+template <int STEPS>
+__device__ __forceinline__ double row16_sum(float f) {
+  static_assert(STEPS == 2 || STEPS == 4, "");
+  f = plus_rot<0x124>(plus_rot<0x128>(f));
+  if constexpr (STEPS == 4) return (double)plus_rot<0x121>(plus_rot<0x122>(f));
+  else return plus_rot<0x121>(plus_rot<0x122>((double)f));
+}
+
+// *p += v in LDS, without waiting for the old value (one lane per address)
+__device__ __forceinline__ void lds_add(double* p, double v) {
+  __builtin_amdgcn_ds_atomic_fadd_f64((__attribute__((address_space(3))) double*)p, v);
 }
 
 template <class T, int L>
@@ -254,9 +267,9 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     }
   };
   // dw += dz^T a over the block's rows, db += dz^T 1 (one of this wave's
-  // M-tiles): products with ones over 32 rows (FP32: 16), FP64 from there
+  // M-tiles): products with ones over 32 rows, FP64 from there
   auto weight_grad = [&](const T* Z, const T* Y, f32x4 (&d)[4][2], double* db) {
-    constexpr int GROUP = F::BF ? 1 : 4;
+    constexpr int GROUP = 32 / KR;
     const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
     f32x4 b = zero;
     double t[4] = {0.0, 0.0, 0.0, 0.0};
@@ -280,7 +293,7 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     }
     if (lr == 0) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) db[mq + 16 * (wave & 3) + 4 * lg + v] += t[v];
+      for (int v = 0; v < 4; ++v) lds_add(&db[mq + 16 * (wave & 3) + 4 * lg + v], t[v]);
     }
   };
   // the thread's index, opaque: the addresses formed from it are computed in
@@ -442,8 +455,8 @@ __global__ __launch_bounds__(TF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const double t = row16_sum((double)dwo[e]);
-          if ((me & 15) == 0) s.dwo[half][u0 + e] += t;
+          const double t = row16_sum<F::BF ? 2 : 4>(dwo[e]);  // 16 (FP32: 32) rows in FP32
+          if ((me & 15) == 0) lds_add(&s.dwo[half][u0 + e], t);
         }
       }
       __syncthreads();
