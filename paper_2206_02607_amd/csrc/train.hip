@@ -301,27 +301,32 @@ __global__ __launch_bounds__(256) void layer1_grad_kernel(const double* __restri
                                                           float* __restrict__ dW1, float* __restrict__ db1,
                                                           float* __restrict__ dq) {
   const int nw = 1 + m, lane = threadIdx.x & 63;
-  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= W * (m + r) + W + B * r) return;
-  double s = 0.0;
-  float* out;
-  if (i < W * (m + r)) {
-    const int u = i / (m + r), k = i % (m + r);
-    for (int b = lane; b < B; b += 64)
-      s += k < m ? S[((int64_t)b * nw + 1 + k) * W + u] : S[((int64_t)b * nw) * W + u] * (double)q[b * r + (k - m)];
-    out = dW1 + i;
-  } else if (i < W * (m + r) + W) {
-    const int u = i - W * (m + r);
-    for (int b = lane; b < B; b += 64) s += S[((int64_t)b * nw) * W + u];
-    out = db1 + u;
-  } else {
-    const int j = i - W * (m + r) - W, b = j / r, k = j % r;
-    for (int u = lane; u < W; u += 64) s += S[((int64_t)b * nw) * W + u] * (double)W1[u * (m + r) + m + k];
-    out = dq + j;
-  }
+  for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < W * (m + r) + W + B * r; i += gridDim.x * 4) {
+    double s = 0.0;
+    float* out;
+    if (i < W * (m + r)) {
+      const int u = i / (m + r), k = i % (m + r);
+      for (int b = lane; b < B; b += 64)
+        s += k < m ? S[((int64_t)b * nw + 1 + k) * W + u] : S[((int64_t)b * nw) * W + u] * (double)q[b * r + (k - m)];
+      out = dW1 + i;
+    } else if (i < W * (m + r) + W) {
+      const int u = i - W * (m + r);
+      for (int b = lane; b < B; b += 64) s += S[((int64_t)b * nw) * W + u];
+      out = db1 + u;
+    } else {
+      const int j = i - W * (m + r) - W, b = j / r, k = j % r;
+      for (int u = lane; u < W; u += 64) s += S[((int64_t)b * nw) * W + u] * (double)W1[u * (m + r) + m + k];
+      out = dq + j;
+    }
 #pragma unroll
-  for (int w = 1; w < 64; w <<= 1) s += __shfl_xor(s, w);
-  if (lane == 0) *out = (float)s;
+    for (int w = 1; w < 64; w <<= 1) s += __shfl_xor(s, w);
+    if (lane == 0) *out = (float)s;
+  }
+}
+// A launch holds fewer than 2^32 threads: from some 4 million outputs (524,000
+// snapshots of 8 latents) on, its waves take several.
+static dim3 layer1_grid(int W, int m, int r, int B) {
+  return dim3((unsigned)std::min<int64_t>(1 << 20, ((int64_t)W * (m + r) + W + (int64_t)B * r + 3) / 4));
 }
 
 __global__ void d2f_kernel(const double* __restrict__ a, float* __restrict__ b, int64_t n) {
@@ -573,9 +578,10 @@ static crom_status fused_fwd_bwd(const crom_net* n, const float* x, int B, int64
   hipLaunchKernelGGL(k, dim3(wgs), dim3(TF_THREADS), sizeof(FusedLds<T, L>), st, a);
   FusedReduceArgs f{ws.part, ws.mpart, ws.cpart, wgs, L, a.chunks, pi, grad, dg_in ? nullptr : loss,
                     (double)((int64_t)B * P), ws.csum, B};
-  hipLaunchKernelGGL(fused_reduce_kernel, dim3(L * TF_MAT / 64 + ((1 + L) * TF_W + 2 + 63) / 64 + B * (3 * TF_W / 64)),
+  hipLaunchKernelGGL(fused_reduce_kernel, dim3(L * TF_MAT / 64 + ((1 + L) * TF_W + 2 + 63) / 64 +
+                                                (unsigned)std::min<int64_t>(1 << 20, (int64_t)B * (3 * TF_W / 64))),
                      dim3(TF_LANES * 64), 0, st, f);
-  hipLaunchKernelGGL(layer1_grad_kernel, dim3((TF_W * (2 + r) + TF_W + B * r + 3) / 4), dim3(256), 0, st, ws.csum, q,
+  hipLaunchKernelGGL(layer1_grad_kernel, layer1_grid(TF_W, 2, r, B), dim3(256), 0, st, ws.csum, q,
                      n->params + pi.w[0], B, TF_W, 2, r, grad + pi.w[0], grad + pi.b[0], dq);
   return hip_check(hipGetLastError(), "fused training pass");
 }
@@ -720,7 +726,7 @@ static crom_status decoder_fwd_bwd(const crom_net* n, const float* x, int B, int
   {
     const int nw = 1 + m;
     colsum<T>(dz, W, W, B, P, x, P, m, nw, ws.cpart, ws.csum, st);
-    hipLaunchKernelGGL(layer1_grad_kernel, dim3((W * (m + r) + W + B * r + 3) / 4), dim3(256), 0, st,
+    hipLaunchKernelGGL(layer1_grad_kernel, layer1_grid(W, m, r, B), dim3(256), 0, st,
                        ws.csum, q, prm + pi.w[0], B, W, m, r, grad + pi.w[0], grad + pi.b[0], dq);
   }
   return hip_check(hipGetLastError(), "decoder backward");
@@ -1057,23 +1063,24 @@ __global__ __launch_bounds__(256) void conv_fwd_kernel(const float* __restrict__
 // order; q2 (NULL: none): a second copy of q.
 __global__ __launch_bounds__(256) void dense_fwd_kernel(const float* __restrict__ x, const float* __restrict__ E1,
                                                        const float* __restrict__ c1, const float* __restrict__ E2,
-                                                       const float* __restrict__ c2, int64_t n_in, int n_mid, int n_out,
+                                                       const float* __restrict__ c2, int B, int64_t n_in, int n_mid, int n_out,
                                                        float* __restrict__ h, float* __restrict__ q,
                                                        float* __restrict__ q2) {
-  const int64_t b = blockIdx.x;
   auto row = [](const float* W, float bias, const float* in, int64_t n) {
     float s = bias;
 #pragma unroll 8
     for (int64_t i = 0; i < n; ++i) s += W[i] * in[i];
     return s;
   };
-  for (int o = threadIdx.x; o < n_mid; o += blockDim.x)
-    h[b * n_mid + o] = elu_f(row(E1 + o * n_in, c1[o], x + b * n_in, n_in));
-  __syncthreads();
-  for (int o = threadIdx.x; o < n_out; o += blockDim.x) {
-    const float s = row(E2 + (int64_t)o * n_mid, c2[o], h + b * n_mid, n_mid);
-    q[b * n_out + o] = s;
-    if (q2) q2[b * n_out + o] = s;
+  for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
+    for (int o = threadIdx.x; o < n_mid; o += blockDim.x)
+      h[b * n_mid + o] = elu_f(row(E1 + o * n_in, c1[o], x + b * n_in, n_in));
+    __syncthreads();
+    for (int o = threadIdx.x; o < n_out; o += blockDim.x) {
+      const float s = row(E2 + (int64_t)o * n_mid, c2[o], h + b * n_mid, n_mid);
+      q[b * n_out + o] = s;
+      if (q2) q2[b * n_out + o] = s;
+    }
   }
 }
 
@@ -1225,8 +1232,8 @@ static crom_status conv_encoder_fwd(const ConvShape& c, const float* prm, const 
   // the flattened top: [B][d][L] is [B][L d] channel-major; with no
   // convolution the snapshot itself ([B][P d], point-major)
   const float* flat = c.nl ? w.a[c.nl] : u;
-  hipLaunchKernelGGL(dense_fwd_kernel, dim3((unsigned)B), dim3(256), 0, st, flat, prm + c.e1, prm + c.c1, prm + c.e2,
-                     prm + c.c2, c.len[c.nl] * c.d, c.hidden, c.r, w.h, w.q, q_out);
+  hipLaunchKernelGGL(dense_fwd_kernel, dim3((unsigned)std::min(B, 1 << 20)), dim3(256), 0, st, flat, prm + c.e1,
+                     prm + c.c1, prm + c.e2, prm + c.c2, B, c.len[c.nl] * c.d, c.hidden, c.r, w.h, w.q, q_out);
   return hip_check(hipGetLastError(), "convolutional encoder forward");
 }
 

@@ -90,9 +90,9 @@ __global__ __launch_bounds__(256) void fused_prep_kernel(const float* __restrict
                                                          float* __restrict__ c) {
   using F = FusedTile<T>;
   const int nf = L * 2 * F::FRAGS;
-  for (int f = blockIdx.x * blockDim.x + threadIdx.x; f < nf + B * TF_W; f += gridDim.x * blockDim.x) {
-    if (f < nf) {
-      const int l = f & 63, kb = (f >> 6) % F::KQ, mt = (f >> 6) / F::KQ % (TF_W / 16), dir = f / F::FRAGS % 2;
+  for (int64_t j = blockIdx.x * blockDim.x + threadIdx.x; j < nf + (int64_t)B * TF_W; j += gridDim.x * blockDim.x) {
+    if (j < nf) {
+      const int f = (int)j, l = f & 63, kb = (f >> 6) % F::KQ, mt = (f >> 6) / F::KQ % (TF_W / 16), dir = f / F::FRAGS % 2;
       const float* Wl = params + pi.w[1 + f / (2 * F::FRAGS)];
       const int m = 32 * (mt >> 1) + 8 * (l >> 2 & 3) + 4 * (mt & 1) + (l & 3), k = F::E * (4 * kb + (l >> 4));
       typename F::frag v;
@@ -100,7 +100,8 @@ __global__ __launch_bounds__(256) void fused_prep_kernel(const float* __restrict
       for (int e = 0; e < F::E; ++e) v[e] = (T)(dir ? Wl[(k + e) * TF_W + m] : Wl[m * TF_W + k + e]);
       frags[f] = v;
     } else {
-      const int i = f - nf, b = i / TF_W, un = i % TF_W;
+      const int64_t i = j - nf, b = i / TF_W;
+      const int un = (int)(i % TF_W);
       const float* W1 = params + pi.w[0];
       double s = params[pi.b[0] + un];
       for (int k = 0; k < r; ++k) s += (double)W1[un * (2 + r) + 2 + k] * q[b * r + k];
@@ -626,13 +627,18 @@ __global__ __launch_bounds__(TF_LANES * 64) void fused_reduce_kernel(FusedReduce
     }
     return;
   }
-  const int i = (blk - nb_w - nb_o) * 64 + t, seg = i / (3 * TF_W), o = i % (3 * TF_W);  // 3 W is a multiple of 64
-  const double* p = a.spart + (size_t)seg * a.chunks * 3 * TF_W + o;
+  const int64_t stride = (int64_t)(gridDim.x - nb_w - nb_o) * 64;
+  for (int64_t i = (int64_t)(blk - nb_w - nb_o) * 64 + t; i - t < (int64_t)a.segs * 3 * TF_W; i += stride) {
+    const int64_t seg = i / (3 * TF_W), o = i % (3 * TF_W);  // 3 W is a multiple of 64
+    const double* p = a.spart + seg * a.chunks * 3 * TF_W + o;
+    s = 0.0;
 #pragma unroll 8
-  for (int ch = lane; ch < a.chunks; ch += TF_LANES) s += p[(size_t)ch * 3 * TF_W];
-  sh[lane][t] = s;
-  __syncthreads();
-  if (threadIdx.x < 64) a.S[i] = total(&sh[0][0]);
+    for (int ch = lane; ch < a.chunks; ch += TF_LANES) s += p[(size_t)ch * 3 * TF_W];
+    sh[lane][t] = s;
+    __syncthreads();
+    if (threadIdx.x < 64) a.S[i] = total(&sh[0][0]);
+    __syncthreads();
+  }
 }
 
 }  // namespace crom

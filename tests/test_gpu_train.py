@@ -658,3 +658,28 @@ def test_fused_pass_edges_fp32(cuda, depth, r, B, P):
     print({k: f"{v:.1e}" for k, v in errs.items()})
     bad = {k: v for k, v in errs.items() if not v <= TOL["fp32"]}
     assert not bad, bad
+
+
+@pytest.mark.parametrize("shape,B", [("2d", 700_000), ("1d", 6_000_000)])
+def test_backward_of_a_million_snapshots(cuda, shape, B):
+    """More snapshots than one launch's 2^32 threads give an output each (a
+    point per snapshot): all but a few cotangents are zero, so the gradients
+    are those of the few alone."""
+    import torch
+    from paper_2206_02607_amd import crom
+    m, r, d, w, depth = SHAPES[shape]
+    g = rng(29)
+    D = crom.Decoder.from_layers(xavier_mlp(g, m, r, d, w, 3, bias_scale=0.2), m, precision="bf16", device=cuda)
+    x = torch.from_numpy(uniform_points(g, 1, m)).to(cuda)
+    some = np.unique(np.concatenate([[0, 1, B // 2, B - 1], g.integers(0, B, 60)]))
+    q = torch.from_numpy(g.uniform(-1, 1, size=(len(some), r)).astype(np.float32)).to(cuda)
+    dg = torch.from_numpy(g.uniform(-1, 1, size=(len(some), 1, 1)).astype(np.float32)).to(cuda)
+    rows = torch.from_numpy(some).to(cuda)
+    Q, DG = torch.zeros(B, r, device=cuda), torch.zeros(B, 1, 1, device=cuda)
+    Q[rows], DG[rows] = q, dg
+    gp, gq = crom.decode_vjp(D, x, Q, DG)
+    rp, rq = crom.decode_vjp(D, x, q, dg)
+    assert torch.equal(gq[rows], rq)
+    gq[rows] = 0
+    assert not gq.any()
+    assert normwise_rel(gp.cpu().numpy(), rp.cpu().numpy()) <= TOL["fp32"]
