@@ -297,11 +297,13 @@ struct ChainPlan {
 // Engine's batches a whole round of Chain costs 4 * 0.87 and a cut one 2.2 *
 // 0.87 (65,536 points 29.6 and 26.2 us, 65,537 31.5 and 37.7, 131,072 52.6 and
 // 48.1).  The sine's epilogue is longer: 0.97 (65,536 points 29.9 and 28.2 us,
-// 82,000 39.1 and 40.1, 100,000 47.1 and 49.3, 131,072 53.7 and 50.1).
+// 82,000 39.1 and 40.1, 100,000 47.1 and 49.3, 131,072 53.7 and 50.1).  The
+// packed weights go straight to LDS, 16 bytes per lane: at a lesser alignment
+// Engine takes them, through registers.
 template <class S>
-static bool chain_takes(int depth, int64_t P, int64_t sets) {
+static bool chain_takes(int depth, int64_t P, int64_t sets, const char* packed) {
   using C = Chain<S>;
-  if (depth < 2 || C::lds_bytes(depth) > LDS_MAX) return false;
+  if (depth < 2 || C::lds_bytes(depth) > LDS_MAX || reinterpret_cast<uintptr_t>(packed) % 16 != 0) return false;
   const int64_t n = ((P + 63) / 64 * sets + C::CUS - 1) / C::CUS;
   const ChainPlan c = ChainPlan::of(P, sets, C::CUS);
   const int64_t rounds = c.full / C::CUS, rest = c.full % C::CUS;

@@ -314,7 +314,7 @@ static crom_status run_pass(const DecodeArgs& a, hipStream_t st) {
   if constexpr (!XT && D2 == D2_NONE && NQ == 0) {
     using C = Cols<S::M, S::R, 1, 0, false, D2_NONE, 0>;
     if constexpr (S::W == 128 && PREC == PREC_BF16) {
-      if (chain_takes<S>(a.depth, a.P, a.B)) return launch_chain<S>(a, st);
+      if (chain_takes<S>(a.depth, a.P, a.B, a.packed)) return launch_chain<S>(a, st);
     }
     return launch_decode<S, C, DecodeTune<S, PREC>::NBV, PREC, ValueTune<S, PREC>>(a, st);
   } else {

@@ -143,7 +143,7 @@ static crom_status residual_prec(int prec, const ResidualArgs& a, int n_set, hip
     case CROM_PREC_FP32: return launch_residual<S, PREC_FP32>(a, n_set, st);
     case CROM_PREC_BF16:
       if constexpr (S::W == 128 && S::D == 1) {
-        if (chain_takes<S>(a.depth, a.P, n_set)) return launch_residual_chain<S>(a, n_set, st);
+        if (chain_takes<S>(a.depth, a.P, n_set, a.packed)) return launch_residual_chain<S>(a, n_set, st);
       }
       return launch_residual<S, PREC_BF16>(a, n_set, st);
     case CROM_PREC_BF16_PURE: return launch_residual<S, PREC_BF16_PURE>(a, n_set, st);

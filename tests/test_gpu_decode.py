@@ -258,3 +258,23 @@ def test_decode_batch_arguments(cuda):
     assert dec.decode_batch(xt[:0], q2).shape == (2, 0, 1)
     with pytest.raises(crom.CromError):
         dec.decode_batch(xt, q2[:, :7])
+
+
+def test_value_decode_unaligned_weights(cuda):
+    """Packed weights at any 4-byte address: many points too (their kernel
+    loads 16 bytes per lane straight to LDS, where they are aligned)."""
+    import torch
+    from paper_2206_02607_amd import crom
+    g = rng(91)
+    layers = xavier_mlp(g, 2, 8, 1, 128, 5, bias_scale=0.2)
+    dec = crom.Decoder.from_layers(layers, 2, precision="bf16", device=cuda)
+    x = torch.from_numpy(uniform_points(g, 70_000, 2)).to(cuda)
+    q = torch.from_numpy(g.uniform(-1, 1, size=(2, 8))).to(cuda)
+    ref = dec.decode_batch(x, q)
+    n = dec.packed.numel()
+    for shift in (4, 8):
+        buf = torch.empty(n + 16, dtype=torch.uint8, device=cuda)
+        dec.packed = buf[shift:shift + n]
+        assert dec.packed.data_ptr() % 16 == shift
+        dec.pack()
+        assert torch.equal(dec.decode_batch(x, q), ref)
