@@ -7,7 +7,7 @@
 // 16,384 points, 0.56 ms in FP32 for 5 of 9,797.  Here a workgroup carries 128
 // rows (FP32: 64) through all layers and back with the activations in LDS and
 // every weight gradient in accumulators, so that memory sees the points, the
-// snapshots and one partial gradient per workgroup: 0.215 ms and 0.26 ms.
+// snapshots and one partial gradient per workgroup: 0.206 ms and 0.26 ms.
 // In bfloat16, of the 62 k cycles a block of rows takes, vector instructions
 // (the ELU and its slope, the conversions) are issued in about 25 k, products
 // in 13 k and LDS is busy in 24 k; the rest waits, at 16 barriers and for LDS.
