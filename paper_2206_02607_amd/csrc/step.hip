@@ -2165,11 +2165,8 @@ static crom_status launch_gn_rounds_t(StepArgs a, int max_rounds, hipStream_t st
       // one workgroup per compute unit: with more, tickets drawn together land
       // on one unit (1D FP32, 64 instances of 1,100 samples, three per SIMD:
       // 540 us, one per unit 500)
-      static ResidentCache rct;
-      int64_t gt = 0;
-      if ((s = resident_grid(rct, reinterpret_cast<const void*>(kt), NW * 64, lds_bytes, &gt)) != CROM_OK) return s;
-      gt = std::max<int64_t>(1, std::min<int64_t>({gt, TAIL_MAX_WG, a.L.nblk_max}));
-      hipLaunchKernelGGL(kt, dim3((unsigned)gt), dim3(NW * 64), lds_bytes, st, a, own + 1, max_rounds);
+      hipLaunchKernelGGL(kt, dim3((unsigned)std::min(TAIL_MAX_WG, a.L.nblk_max)), dim3(NW * 64), lds_bytes, st, a,
+                         own + 1, max_rounds);
     }
   }
   timer_mark(st);
